@@ -638,12 +638,30 @@ __global__ __launch_bounds__(256) void k_cg_pupdate(CgArgs a)
     }
 }
 
+// What follows a pair of sums (s0, s1): stored in the geometry's scalars (slot < 0: not
+// stored), then, for a live geometry, the scalar recurrence `mode`: 0 alpha = rr / pAp; 1
+// beta = rr_new / rr, rr = rr_new; 2 rr = rr_new (start); -1 none; -2 none, and only
+// geometries whose CG_REPL slot is set are written.
+__device__ __forceinline__ void cg_scalars(double *s, double s0, double s1, int slot0, int slot1, int mode)
+{
+    if (mode == -2 && s[CG_REPL] == 0.0) return;  // only the geometries just replaced
+    if (slot0 >= 0) s[slot0] = s0;
+    if (slot1 >= 0) s[slot1] = s1;
+    if (mode >= 0 && s[CG_DONE] == 0.0) {
+        if (mode == 0) {
+            s[CG_ALPHA] = s[CG_PAP] > 0.0 ? s[CG_RR] / s[CG_PAP] : 0.0;
+        } else if (mode == 1) {
+            s[CG_BETA] = s[CG_RR] > 0.0 ? s[CG_RRNEW] / s[CG_RR] : 0.0;
+            s[CG_RR] = s[CG_RRNEW];
+        } else {
+            s[CG_RR] = s[CG_RRNEW];
+        }
+    }
+}
+
 // Per-geometry sums of the per-block partial pairs: geometry g owns blocks
 // [block0_g, block0_{g+1}); one workgroup per geometry, fixed summation order.
-// dst[g*CG_NSCAL + slot0 + k] = sum (k = 0, 1; slot < 0 skips that lane); then, for a
-// live geometry, the scalar recurrence `mode`: 0 alpha = rr / pAp; 1 beta = rr_new / rr,
-// rr = rr_new; 2 rr = rr_new (start); -1 none; -2 none, and only geometries whose CG_REPL
-// slot is set are written.
+// then cg_scalars.
 __global__ __launch_bounds__(256) void k_cg_segsum(const double *part, const GeomInfo *geom,
                                                    int ngeom, int nb, double *scal, int slot0,
                                                    int slot1, int mode)
@@ -684,25 +702,72 @@ __global__ __launch_bounds__(256) void k_cg_segsum(const double *part, const Geo
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        double *s = scal + g * CG_NSCAL;
-        if (mode == -2 && s[CG_REPL] == 0.0) return;  // only the geometries just replaced
-        if (slot0 >= 0) s[slot0] = sh[0][0];
-        if (slot1 >= 0) s[slot1] = sh[1][0];
-        // then the scalar recurrence of this geometry (live ones only)
-        if (mode >= 0 && s[CG_DONE] == 0.0) {
-            if (mode == 0) {
-                s[CG_ALPHA] = s[CG_PAP] > 0.0 ? s[CG_RR] / s[CG_PAP] : 0.0;
-            } else if (mode == 1) {
-                s[CG_BETA] = s[CG_RR] > 0.0 ? s[CG_RRNEW] / s[CG_RR] : 0.0;
-                s[CG_RR] = s[CG_RRNEW];
-            } else {
-                s[CG_RR] = s[CG_RRNEW];
-            }
-        }
-    }
+    if (threadIdx.x == 0) cg_scalars(scal + g * CG_NSCAL, sh[0][0], sh[1][0], slot0, slot1, mode);
 }
 
+// The same for one long block list in one launch: workgroup g sums rows [g * chunk, (g + 1)
+// * chunk) into mid[g], and the last workgroup to arrive (a ticket in `count`, left at 0
+// for the next launch) sums those and runs cg_scalars.  Nothing waits for another
+// workgroup, and the order of every addition is fixed: thread t of a range adds rows t, t
+// + 256, ..., then a tree (threads 128, 64, ... apart), as k_finish_rows adds them.  On a
+// 208^3 foam (17 000 rows) it takes 8.0 us where three launches (ranges, range sums,
+// scalars) took 15.0, twice per iteration beside 46 + 32 us of the CG kernels; one workgroup
+// of 1024 threads took 14.6 (one CU's bandwidth), so the ranges stay spread over the chip.
+constexpr int CG_RANGES = 256;
+__device__ __forceinline__ double range_tree(const double *sh, int lane)  // 256 values, in wave 0
+{
+    return wave_sum((sh[lane] + sh[lane + 128]) + (sh[lane + 64] + sh[lane + 192]));
+}
+__global__ __launch_bounds__(256) void k_cg_segsum_long(const double2 *part, int nb, int chunk, double *mid,
+                                                        uint32_t *count, double *scal, int slot0, int slot1, int mode)
+{
+    __shared__ double sh[2][256];
+    const int g = blockIdx.x, t = threadIdx.x, r1 = min((g + 1) * chunk, nb);
+    double s0 = 0.0, s1 = 0.0;
+    int i = g * chunk + t;
+    for (; i + 3 * 256 < r1; i += 4 * 256) {  // four rows' loads in flight
+        double2 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = part[i + k * 256];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            s0 += v[k].x;
+            s1 += v[k].y;
+        }
+    }
+    for (; i < r1; i += 256) {
+        const double2 v = part[i];
+        s0 += v.x;
+        s1 += v.y;
+    }
+    sh[0][t] = s0;
+    sh[1][t] = s1;
+    __syncthreads();
+    if (t >= 64) return;  // whole waves
+    s0 = range_tree(sh[0], t);
+    s1 = range_tree(sh[1], t);
+    uint32_t arrived = 0u;
+    if (t == 0) {
+        __hip_atomic_store(mid + 2 * g, s0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(mid + 2 * g + 1, s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        arrived = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__builtin_amdgcn_readfirstlane(arrived) != gridDim.x - 1) return;
+    double m0[4], m1[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int j = t + 64 * k;
+        const bool in = j < (int)gridDim.x;
+        m0[k] = in ? __hip_atomic_load(mid + 2 * j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+        m1[k] = in ? __hip_atomic_load(mid + 2 * j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+    }
+    s0 = wave_sum((m0[0] + m0[2]) + (m0[1] + m0[3]));
+    s1 = wave_sum((m1[0] + m1[2]) + (m1[1] + m1[3]));
+    if (t == 0) {
+        __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        cg_scalars(scal, s0, s1, slot0, slot1, mode);
+    }
+}
 
 // ---- initial guess of the unit-drop problem: 6-connected clusters on the GPU ----
 // Lock-free union-find over the slots, after the hooking and pointer-jumping scheme of
@@ -1351,18 +1416,20 @@ int ir_launch_fold(int storage, int B, const CgArgs &a, int64_t nslots, void *st
 #undef IR_FOLD
     return (int)hipGetLastError();
 }
+static uint32_t *cg_ticket(const CgArgs &a) { return (uint32_t *)(a.mid + 2 * CG_RANGES); }
+int cg_launch_start(const CgArgs &a, void *stream)
+{
+    const int e = rd_launch_fill_u32(a.scal, 0u, (int64_t)a.ngeom * CG_NSCAL * 2, stream);
+    return e || !a.mid ? e : rd_launch_fill_u32(cg_ticket(a), 0u, 1, stream);
+}
 int cg_launch_segsum(const CgArgs &a, int slot0, int slot1, int mode, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
     if (a.ngeom == 1 && a.mid && a.nb > 4096) {
-        // one long block list: fixed row ranges over 256 workgroups, then their sums, then
-        // the recurrence on that single row (one workgroup over millions of rows would
-        // take as long as a matvec)
-        double *sum = a.mid + 1024;
-        const int e = rd_launch_finish_reduce(a.partial, a.nb, 2, a.mid, sum, stream);
-        if (e) return e;
-        hipLaunchKernelGGL(k_cg_segsum, dim3(1), dim3(256), 0, st, (const double *)sum, a.geom, 1, 1, a.scal, slot0,
-                           slot1, mode);
+        // one workgroup over this many rows would take longer than the ranges and the ticket
+        const int chunk = (a.nb + CG_RANGES - 1) / CG_RANGES;
+        hipLaunchKernelGGL(k_cg_segsum_long, dim3((unsigned)((a.nb + chunk - 1) / chunk)), dim3(256), 0, st,
+                           (const double2 *)a.partial, a.nb, chunk, a.mid, cg_ticket(a), a.scal, slot0, slot1, mode);
         return (int)hipGetLastError();
     }
     hipLaunchKernelGGL(k_cg_segsum, dim3((unsigned)a.ngeom), dim3(256), 0, st, (const double *)a.partial, a.geom,

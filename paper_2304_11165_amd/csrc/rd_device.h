@@ -504,10 +504,29 @@ __device__ __forceinline__ void stage_tile(float (*tile)[Blk<B>::TL], const T *c
     }
 }
 
-// Wave-level FP64 sum in a fixed butterfly order (deterministic).
+// Wave-level FP64 sum in a fixed butterfly order (deterministic): partners 32, 16, 8, 4, 2
+// and 1 lanes away.  All 64 lanes must be active.  The half and row swaps and the row
+// rotations stay in the vector unit (after the step of distance 2 d every value repeats
+// with period 2 d inside a row, so a rotation by d brings the partner's), where a shuffle
+// through LDS takes two permutes and their latency per step.
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    auto join = [](uint32_t lo, uint32_t hi) { return __hiloint2double((int)hi, (int)lo); };
+    uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    v = join(l[0], h[0]) + join(l[1], h[1]);
+    lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = join(l[0], h[0]) + join(l[1], h[1]);
+#define RD_ROT_ADD(D)                                                                               \
+    v += join((uint32_t)__builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + D, 0xf, 0xf, true), \
+              (uint32_t)__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + D, 0xf, 0xf, true))
+    RD_ROT_ADD(8);
+    RD_ROT_ADD(4);
+    RD_ROT_ADD(2);
+    RD_ROT_ADD(1);
+#undef RD_ROT_ADD
     return v;
 }

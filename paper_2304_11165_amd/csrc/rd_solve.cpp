@@ -170,7 +170,7 @@ rd_status run_cg(const CgArgs &args, int storage, int B, hipStream_t st, int axi
     CgArgs a = args;  // B = 8 swaps the two p buffers every iteration
     const int n = a.ngeom;
     out.assign(n, CgOut());
-    LAUNCHCHK(rd_launch_fill_u32(a.scal, 0u, (int64_t)n * CG_NSCAL * 2, st));
+    LAUNCHCHK(cg_launch_start(a, st));
     if (!a.x64) return rd_fail(RD_ERR_STATE, "CG needs the FP64 iterate");
     if (B != 8) a.prec = 0;
     LAUNCHCHK(cg_launch_res64(storage, B, a, 1, st));

@@ -41,8 +41,8 @@ struct CgArgs {
     void *p2;              // second p buffer (B = 8: the fused p update writes here)
     double *partial;       // [nb][2]
     double *scal;          // [ngeom][CG_NSCAL]
-    double *mid;           // single geometry: scratch of >= 1040 doubles for two-level sums
-                           // of long block lists (NULL: one workgroup per geometry)
+    double *mid;           // single geometry: scratch of >= 513 doubles for the sums of long
+                           // block lists (NULL: one workgroup per geometry)
     void *z;               // B = 8 with prec > 0: the preconditioned residual z = M^-1 r
     int prec;              // B = 8: Jacobi steps of the block preconditioner (0: plain CG)
 };
@@ -60,6 +60,8 @@ int cg_launch_prec(int storage, const CgArgs &a, void *stream);
 int cg_launch_pupdate(int storage, int B, const CgArgs &a, void *stream);
 // per-block FP64 partials (inlet, outlet) of the flux of x64 through the Dirichlet planes
 int cg_launch_flux(int B, const CgArgs &a, int inlet_face, void *stream);
+// the scalars (and the ticket of the long lists' sums) zeroed, before the first sum
+int cg_launch_start(const CgArgs &a, void *stream);
 int cg_launch_segsum(const CgArgs &a, int slot0, int slot1, int mode, void *stream);
 // Initial guess of the unit-drop problem along `axis` into a.x (every slot, rounded to
 // the storage type) and a.x64 (FP64), from the
