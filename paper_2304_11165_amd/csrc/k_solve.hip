@@ -163,6 +163,16 @@ __device__ __forceinline__ float cg_inv_count(unsigned code)
     return n ? __builtin_amdgcn_rcpf((float)n) : 0.0f;
 }
 
+// Group of four blocks of this workgroup.  Consecutive workgroups go round-robin to the 8
+// XCDs, so y and z neighbours would always sit behind another XCD's L2; instead each XCD
+// takes `run` consecutive groups out of every 8 * run (cg_xcd_run), which keeps most y
+// faces in its own L2 while all XCDs stay in one part of the block list.
+__device__ __forceinline__ int cg_group(int run)
+{
+    const int id = (int)blockIdx.x, r = id & (8 * run - 1);  // run: a power of 2
+    return id - r + (r & 7) * run + (r >> 3);
+}
+
 template <int B>
 __device__ __forceinline__ bool geom_live(const CgArgs &a, int gid)
 {
@@ -236,7 +246,7 @@ __global__ __launch_bounds__(256) void k_cg_matvec8(CgArgs a)
     __shared__ float tile[4][100];
     __shared__ float xch[4][2][64];  // x = 0 / x = 7 planes of each wave's p_new, [z * 8 + y]
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int b = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + wv);
+    const int b = __builtin_amdgcn_readfirstlane(cg_group(a.xcd_run) * 4 + wv);
     if (b >= a.nb) {
         __syncthreads();
         return;
@@ -370,7 +380,7 @@ __global__ __launch_bounds__(256) void k_cg_update8(CgArgs a)
 {
     __shared__ float tile[4][100];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int b = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + wv);
+    const int b = __builtin_amdgcn_readfirstlane(cg_group(a.xcd_run) * 4 + wv);
     if (b >= a.nb) return;
     const BlockInfo bi = a.info[b];
     int bx, by, bz, gid;
@@ -1279,9 +1289,21 @@ int cg_launch_matvec(int storage, int B, const CgArgs &a, void *stream)
 {
     CG_DISPATCH(storage, B, k_cg_matvec, grid_for(B, a.nb), stream, a);
 }
+// Runs of 64 groups, 16 for short lists and for batches (where a long run of a converged
+// geometry's blocks leaves its XCD idle).  k_cg_update8 / k_cg_matvec8 in us, plain order
+// and here: foam 100^3 11.9 / 7.6 and 11.2 / 7.1; 208^3 45.7 / 32.4 and 40.0 / 25.9; 512^3
+// 627 / 374 and 607 / 345; 700^3 1554 / 1118 and 1561 / 854; 16 packings of 48^3 to 144^3
+// 69.1 / 45.1 and 64.3 / 38.9 (one run per XCD: 84 / 50, and slower than the plain order in
+// the update from 512^3 on).
+int cg_xcd_run(int nb, int ngeom) { return ngeom == 1 && nb >= 16384 ? 64 : 16; }
+static dim3 cg_grid8(const CgArgs &a)
+{
+    const int groups = (a.nb + 3) / 4, per = 8 * a.xcd_run;
+    return dim3((unsigned)(std::max(1, (groups + per - 1) / per) * per));  // the last may pass the list's end
+}
 int cg_launch_matvec_fused(int storage, const CgArgs &a, void *stream)
 {
-    const dim3 grid((unsigned)std::max(1, (a.nb + 3) / 4));
+    const dim3 grid = cg_grid8(a);
     hipStream_t st = (hipStream_t)stream;
     if (storage == 0) hipLaunchKernelGGL((k_cg_matvec8<float>), grid, dim3(256), 0, st, a);
     else if (storage == 1) hipLaunchKernelGGL((k_cg_matvec8<bf16_t>), grid, dim3(256), 0, st, a);
@@ -1291,7 +1313,7 @@ int cg_launch_matvec_fused(int storage, const CgArgs &a, void *stream)
 int cg_launch_update(int storage, int B, const CgArgs &a, void *stream)
 {
     if (B == 8) {  // column form with A p recomputed (the fused matvec does not store it)
-        const dim3 grid((unsigned)std::max(1, (a.nb + 3) / 4));
+        const dim3 grid = cg_grid8(a);
         hipStream_t st = (hipStream_t)stream;
         const bool x64 = a.x64 && a.x64_direct, prec = a.prec > 0;
 #define UPD8(T_)                                                                                   \

@@ -173,6 +173,7 @@ rd_status run_cg(const CgArgs &args, int storage, int B, hipStream_t st, int axi
     LAUNCHCHK(cg_launch_start(a, st));
     if (!a.x64) return rd_fail(RD_ERR_STATE, "CG needs the FP64 iterate");
     if (B != 8) a.prec = 0;
+    a.xcd_run = cg_xcd_run(a.nb, n);
     LAUNCHCHK(cg_launch_res64(storage, B, a, 1, st));
     LAUNCHCHK(cg_launch_segsum(a, CG_RRNEW, CG_BB, 2, st));
     if (a.prec > 0) {  // z = M^-1 r; CG_RR becomes r.z

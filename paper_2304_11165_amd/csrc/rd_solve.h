@@ -44,9 +44,11 @@ struct CgArgs {
     double *mid;           // single geometry: scratch of >= 513 doubles for the sums of long
                            // block lists (NULL: one workgroup per geometry)
     void *z;               // B = 8 with prec > 0: the preconditioned residual z = M^-1 r
+    int xcd_run;           // B = 8: consecutive groups of four blocks per XCD (cg_xcd_run)
     int prec;              // B = 8: Jacobi steps of the block preconditioner (0: plain CG)
 };
 
+int cg_xcd_run(int nb, int ngeom);
 int cg_launch_matvec(int storage, int B, const CgArgs &a, void *stream);
 // B = 8: p2 = z + beta p (per live geometry, rounded to the storage type; z = r when
 // a.prec is 0) and the partial (p2.A p2, 0); A p2 is not stored.  The caller then swaps
