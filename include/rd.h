@@ -194,8 +194,8 @@ rd_status rd_sim_clear_dirichlet(rd_sim *sim, int species);
  * implementation using OpenFPM"): steps per captured graph (>= 1), whether rd_sim_step
  * replays a captured hipGraph (1) or launches directly (0), and whether workgroups
  * are remapped so each of the 8 XCDs walks one contiguous range of the block list
- * (xcd_map = 1; its L2 then holds most halo reads).  Results are bitwise
- * identical for every choice. */
+ * (xcd_map = 1; its L2 then holds most halo reads; 0: the list in order, in runs per XCD
+ * the library chooses).  Results are bitwise identical for every choice. */
 rd_status rd_sim_set_launch(rd_sim *sim, int graph_steps, int use_graph, int xcd_map);
 /* Field layout in HBM, before rd_sim_bind (RD_ERR_STATE after it).  The paper stores
  * whole chunks of 8^3 points with an allocation mask (section "Parallel implementation

@@ -242,7 +242,7 @@ template <typename T>
 int launch_t(const StepArgs &a, hipStream_t st)
 {
     int groups = (a.nb + 3) / 4;
-    if (a.xcd_chunk > 0) groups = 8 * a.xcd_chunk;
+    groups = rd_xcd_grid(groups, a.xcd_chunk);
     switch (a.S) {
     case 1: launch_s<T, 1>(a, groups, st); break;
     case 2: launch_s<T, 2>(a, groups, st); break;

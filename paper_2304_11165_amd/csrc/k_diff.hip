@@ -535,7 +535,7 @@ void launch_diff_s(const DiffArgs &a, int column, hipStream_t st)
 {
     if (B == 8 && column) {
         int groups = (a.s.nb + 3) / 4;
-        if (a.s.xcd_chunk > 0) groups = 8 * a.s.xcd_chunk;
+        groups = rd_xcd_grid(groups, a.s.xcd_chunk);
         if (column == 2) hipLaunchKernelGGL((k_step8e<T, S, true>), dim3(groups), dim3(256), 0, st, a);
         else hipLaunchKernelGGL((k_step8e<T, S, false>), dim3(groups), dim3(256), 0, st, a);
     } else {

@@ -1323,7 +1323,7 @@ int launch_step_t(const StepArgs &a, hipStream_t st)
     // blocks per workgroup: 1 for the B = 8 workgroup kernel, 4 for the wave kernels
     const int bpw = (B == 8 && a.kernel < 2) ? 1 : 4;
     int groups = (a.nb + bpw - 1) / bpw;
-    if (a.xcd_chunk > 0) groups = 8 * a.xcd_chunk;
+    groups = rd_xcd_grid(groups, a.xcd_chunk);
     switch (a.S) {
     case 1: launch_step_s<T, B, 1>(a, groups, st); break;
     case 2: launch_step_s<T, B, 2>(a, groups, st); break;

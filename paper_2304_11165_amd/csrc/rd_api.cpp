@@ -661,8 +661,7 @@ rd_status rd_sim::launch_steps(double dt, int64_t n)
             // unless the workgroup-per-block kernel is chosen (then one thread per slot);
             // B = 4: one thread per slot
             const int column = g->B == 8 && kernel != 0 ? (kernel == 3 ? 2 : 1) : 0;
-            const int groups = (a.nb + 3) / 4;
-            a.xcd_chunk = column && xcd_map && groups >= 64 ? (groups + 7) / 8 : 0;
+            a.xcd_chunk = column ? rd_xcd_order((a.nb + 3) / 4, xcd_map) : 0;
             DiffArgs da{a, (const float *)(ws + L.diff), {0.0f, 0.0f, 0.0f, 0.0f}};
             for (int s = 0; s < S; ++s) da.sink[s] = band_on ? (float)(dt * sink[s]) : 0.0f;
             LAUNCHCHK(rd_launch_step_diff(storage, g->B, da, column, stream));
@@ -681,12 +680,11 @@ rd_status rd_sim::launch_steps(double dt, int64_t n)
 
 int rd_sim::xcd_chunk(int nb) const
 {
-    if (!xcd_map) return 0;
-    // blocks per workgroup: 1 for the B = 8 workgroup kernels, 4 for the wave kernels
-    const int bpw = (g->B == 8 && kernel < 2) ? 1 : 4;
-    const int groups = (nb + bpw - 1) / bpw;
-    if (groups < 64) return 0;
-    return (groups + 7) / 8;
+    // the persistent kernel splits the list itself (by XCD only if asked to)
+    if (g->B == 8 && kernel == 1) return xcd_map && nb >= 64 ? (nb + 7) / 8 : 0;
+    // blocks per workgroup: 1 for the B = 8 workgroup kernel, 4 for the wave kernels
+    const int bpw = g->B == 8 && kernel == 0 ? 1 : 4;
+    return rd_xcd_order((nb + bpw - 1) / bpw, xcd_map);
 }
 
 rd_status rd_sim::step(double dt, int64_t n)

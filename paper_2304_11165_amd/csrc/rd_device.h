@@ -465,14 +465,13 @@ struct Cfg {
     static constexpr int VPT = Blk<B>::NS / TPB;  // voxels per thread
 };
 
-// Map a workgroup id to a group of blocks.  With xcd_chunk > 0 the consecutive
-// workgroups that the dispatcher sends round-robin to the 8 XCDs are remapped so
-// that each XCD walks one contiguous range of the block list (its own L2 then
-// holds the +-x / +-y neighbours it needs).
-__device__ __forceinline__ int map_group(int wg, int xcd_chunk)
+// The group of blocks of a workgroup in the order of rd_xcd_order.
+__device__ __forceinline__ int map_group(int wg, int order)
 {
-    if (xcd_chunk <= 0) return wg;
-    return (wg & 7) * xcd_chunk + (wg >> 3);
+    if (order > 0) return (wg & 7) * order + (wg >> 3);
+    if (order == 0) return wg;
+    const int run = -order, r = wg & (8 * run - 1);
+    return wg - r + (r & 7) * run + (r >> 3);
 }
 
 // Stage S fields (species-major, sstride apart) of block b and its six face halos
