@@ -146,8 +146,16 @@ __device__ __forceinline__ int pix(int x, int y) { return (y + 1) * 10 + (x + 1)
 // slots give 0); plane z of every species and of the factor goes to LDS with its
 // four side halos, the z neighbours stay in registers.  Whole 128-byte sectors that
 // hold an active voxel are stored.  XCH: the x faces of x-adjacent blocks of one
-// workgroup are handed over through LDS instead of being read again.
-template <typename T, int S, bool XCH>
+// workgroup are handed over through LDS instead of being read again.  BAND: the sink of
+// the near-surface band (code bit 7) is applied; without it the code bytes are not read.
+// The operations per voxel are rd_update_e's, in its order, with a face toward an
+// inactive neighbour weighted 0 (which leaves the sum as it is) and each z face's weight
+// and difference formed once for the two voxels it joins (they differ in sign only).
+// Bound by memory traffic (about 6.5 TB/s past L2 on the half-full blocks of the 320^3 soil
+// volume, two species: 68.0 us); with a test of code bits and a select per species and face,
+// 950 vector instructions per wave instead of 695, it took 69.5 us, and on volumes of one
+// round of waves (160^3 packing, one species) 15.7 us instead of 14.5.
+template <typename T, int S, bool XCH, bool BAND>
 __global__ __launch_bounds__(256) void k_step8e(DiffArgs d)
 {
     __shared__ float tile[4][S + 1][100];  // species tiles, then the factor's
@@ -161,8 +169,17 @@ __global__ __launch_bounds__(256) void k_step8e(DiffArgs d)
         return;
     }
     const T *cin = (const T *)a.cin;
-    T *cout = (T *)a.cout;
     const int64_t base = (int64_t)b * 512;
+    // the block's slabs in scalar registers; every access is a base plus a 32-bit offset
+    const T *cinb[S];
+    T *coutb[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        cinb[s] = uniform_ptr(cin + s * a.sstride + base);
+        coutb[s] = uniform_ptr((T *)a.cout + s * a.sstride + base);
+    }
+    const float *eb = uniform_ptr(d.e + base);
+    const uint8_t *cb = uniform_ptr(a.code + base);
     const int lx = lane & 7, ly = lane >> 3;
     // the block record whole and unconditionally: one scalar load instead of a load per
     // neighbour index behind the tests below
@@ -171,35 +188,33 @@ __global__ __launch_bounds__(256) void k_step8e(DiffArgs d)
     // x neighbours inside this workgroup (wave-uniform; only with XCH)
     const bool xm_in = XCH && wv > 0 && nbr[0] == b - 1;
     const bool xp_in = XCH && wv < 3 && nbr[1] == b + 1;
-    const uint64_t *rec = a.mask + (int64_t)b * 16;
-    uint64_t Wo[8], Wf[6];
-#pragma unroll
-    for (int z = 0; z < 8; ++z) Wo[z] = rec[z];
-#pragma unroll
-    for (int f = 0; f < 6; ++f) Wf[f] = rec[8 + f];
+    BlockMasks M;
+    M.load(a.mask + (int64_t)b * 16);
 
     typedef typename RawOf<T>::type R;
     R rc[S][8], rh[6][S];
     float ec[8], eh[6];
     unsigned cd[8];
+    const uint32_t ncw = a.ncnt[(int64_t)b * 64 + lane];  // the lane's active-neighbour counts
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
 #pragma unroll
         for (int s = 0; s < S; ++s) rc[s][z] = (R)0;
         ec[z] = 0.0f;
         cd[z] = 0u;
-        if (lane_bit(Wo[z])) {
+        if (lane_bit(M.Wo[z])) {
+            const uint32_t o = (uint32_t)(z * 64 + lane);
 #pragma unroll
-            for (int s = 0; s < S; ++s) rc[s][z] = ld_raw(cin, s * a.sstride + base + z * 64 + lane);
-            ec[z] = d.e[base + z * 64 + lane];
-            cd[z] = (unsigned)a.code[base + z * 64 + lane];
+            for (int s = 0; s < S; ++s) rc[s][z] = ld_raw(at_byte(cinb[s], o * (uint32_t)sizeof(T)), 0);
+            ec[z] = *at_byte(eb, o * 4u);
+            if (BAND) cd[z] = (unsigned)*at_byte(cb, o);
         }
     }
     // face halos: lane (u, v) = (lx, ly) reads the neighbour slot across face f at face
     // coordinates (u, v); a face bit is set only when the neighbour block exists
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
-        int ns;
+        uint32_t ns;
         switch (f) {
         case 0: ns = (ly * 8 + lx) * 8 + 7; break;  // (x=7, y=u, z=v)
         case 1: ns = (ly * 8 + lx) * 8 + 0; break;  // (x=0, y=u, z=v)
@@ -209,14 +224,15 @@ __global__ __launch_bounds__(256) void k_step8e(DiffArgs d)
         default: ns = (0 * 8 + ly) * 8 + lx; break; // (x=u, y=v, z=0)
         }
         const int n = nbr[f];
-        const int64_t hb = (int64_t)(n >= 0 ? n : b) * 512 + ns;
+        const int64_t nb0 = (int64_t)(n >= 0 ? n : b) * 512;
 #pragma unroll
         for (int s = 0; s < S; ++s) rh[f][s] = (R)0;
         eh[f] = 0.0f;
-        if (lane_bit((f == 0 && xm_in) || (f == 1 && xp_in) ? 0ull : Wf[f])) {
+        if (lane_bit((f == 0 && xm_in) || (f == 1 && xp_in) ? 0ull : M.Wf[f])) {
 #pragma unroll
-            for (int s = 0; s < S; ++s) rh[f][s] = ld_raw(cin, s * a.sstride + hb);
-            eh[f] = d.e[hb];
+            for (int s = 0; s < S; ++s)
+                rh[f][s] = ld_raw(at_byte(uniform_ptr(cin + s * a.sstride + nb0), ns * (uint32_t)sizeof(T)), 0);
+            eh[f] = *at_byte(uniform_ptr(d.e + nb0), ns * 4u);
         }
     }
     float c[S][8], side[4][S], zlo[S], zhi[S];
@@ -258,6 +274,11 @@ __global__ __launch_bounds__(256) void k_step8e(DiffArgs d)
     const int gx = bx * 8 + lx, gy = by * 8 + ly;
     const bool bnd = block_on_box(g, bx, by, bz);
     const uint32_t key = diff_key(a);
+    // weight of a face (0 toward an inactive neighbour)
+    auto weight = [](float ep, float eq, uint64_t both) { return lane_bit(both) ? 0.5f * (ep + eq) : 0.0f; };
+    float wdn = weight(ec[0], eh[4], M.pair(0, 4)), dup[S];  // the z face below, c above - c below
+#pragma unroll
+    for (int s = 0; s < S; ++s) dup[s] = c[s][0] - zlo[s];
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
         // plane z and its ring: the side halos of plane z are held by the lanes with
@@ -288,37 +309,50 @@ __global__ __launch_bounds__(256) void k_step8e(DiffArgs d)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
         const int gz = bz * 8 + z;
-        const unsigned code = cd[z];
-        const unsigned m = code & 63u;
-        const bool act = (code & 64u) != 0u;
+        const float nact = (float)((ncw >> (3 * z)) & 7u);
         unsigned onf = 0u;
         if (bnd) onf = faces_on_box(g, gx, gy, gz);
-        const int nwall = __popc(~onf & ~m & 0x3fu);
+        const float nwall = (6.0f - nact) - (float)__popc(onf);
         const float *pe = &tile[wv][S][pix(lx, ly)];
-        const float ev[6] = {pe[-1], pe[1], pe[-10], pe[10], z == 0 ? eh[4] : ec[z > 0 ? z - 1 : 0],
-                             z == 7 ? eh[5] : ec[z < 7 ? z + 1 : 7]};
+        const float ws[4] = {weight(ec[z], pe[-1], M.pair(z, 0)), weight(ec[z], pe[1], M.pair(z, 1)),
+                             weight(ec[z], pe[-10], M.pair(z, 2)), weight(ec[z], pe[10], M.pair(z, 3))};
+        const float wup = weight(ec[z], z == 7 ? eh[5] : ec[z < 7 ? z + 1 : 7], M.pair(z, 5));
         float cen[S], res[S];
 #pragma unroll
         for (int s = 0; s < S; ++s) cen[s] = c[s][z];
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const float *p = &tile[wv][s][pix(lx, ly)];
-            const float dn = z == 0 ? zlo[s] : c[s][z > 0 ? z - 1 : 0];
-            const float up = z == 7 ? zhi[s] : c[s][z < 7 ? z + 1 : 7];
-            const float nbv[6] = {p[-1], p[1], p[-10], p[10], dn, up};
-            const float sk = (code & RD_CODE_BAND) ? d.sink[s] : 0.0f;
-            const float upd = rd_update_e<S>(cen[s], nbv, ev, ec[z], m, nwall, a.coef[s], sk, cen);
-            const bool isd = (onf & a.coef[s].dir) != 0u;
-            res[s] = act ? (isd ? cen[s] : upd) : 0.0f;
+            const float uc = cen[s], dlo = dup[s];
+            dup[s] = (z == 7 ? zhi[s] : c[s][z < 7 ? z + 1 : 7]) - uc;
+            float lap = 0.0f;
+            lap = fmaf(ws[0], p[-1] - uc, lap);
+            lap = fmaf(ws[1], p[1] - uc, lap);
+            lap = fmaf(ws[2], p[-10] - uc, lap);
+            lap = fmaf(ws[3], p[10] - uc, lap);
+            lap = fmaf(wdn, -dlo, lap);
+            lap = fmaf(wup, dup[s], lap);
+            float r = fmaf(a.coef[s].alpha, lap, uc);
+            float loss = fmaf(a.coef[s].gamma, nwall, a.coef[s].beta);
+            if (BAND) loss = loss + ((cd[z] & RD_CODE_BAND) ? d.sink[s] : 0.0f);
+            r = fmaf(-loss, uc, r);
+#pragma unroll
+            for (int q = 0; q < S; ++q) r = fmaf(a.coef[s].K[q], cen[q], r);
+            if (bnd) {  // Dirichlet voxels lie on the box faces: boundary blocks only (uniform)
+                if ((onf & a.coef[s].dir) != 0u) r = uc;
+            }
+            res[s] = lane_bit(M.Wo[z]) ? r : 0.0f;
         }
+        wdn = wup;
         // every lane has read plane z before any lane overwrites it with plane z + 1
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (lane_bit(sector_lanes<T>(Wo[z]))) {
+        if (lane_bit(sector_lanes<T>(M.Wo[z]))) {
             const uint32_t h = a.sround ? sr_voxel(g, gx, gy, gz, key) : 0u;
 #pragma unroll
-            for (int s = 0; s < S; ++s) diff_store(a, cout, s, s * a.sstride + base + z * 64 + lane, h, res[s]);
+            for (int s = 0; s < S; ++s)
+                diff_store(a, at_byte(coutb[s], (uint32_t)(z * 64 + lane) * (uint32_t)sizeof(T)), s, 0, h, res[s]);
         }
     }
 }
@@ -536,8 +570,12 @@ void launch_diff_s(const DiffArgs &a, int column, hipStream_t st)
     if (B == 8 && column) {
         int groups = (a.s.nb + 3) / 4;
         groups = rd_xcd_grid(groups, a.s.xcd_chunk);
-        if (column == 2) hipLaunchKernelGGL((k_step8e<T, S, true>), dim3(groups), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((k_step8e<T, S, false>), dim3(groups), dim3(256), 0, st, a);
+        bool band = false;
+        for (int s = 0; s < S; ++s) band = band || a.sink[s] != 0.0f;
+        if (column == 2 && band) hipLaunchKernelGGL((k_step8e<T, S, true, true>), dim3(groups), dim3(256), 0, st, a);
+        else if (column == 2) hipLaunchKernelGGL((k_step8e<T, S, true, false>), dim3(groups), dim3(256), 0, st, a);
+        else if (band) hipLaunchKernelGGL((k_step8e<T, S, false, true>), dim3(groups), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((k_step8e<T, S, false, false>), dim3(groups), dim3(256), 0, st, a);
     } else {
         const int64_t n = (int64_t)a.s.nb * B * B * B;
         hipLaunchKernelGGL((k_step_diff<T, B, S>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);

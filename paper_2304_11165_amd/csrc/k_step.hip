@@ -48,34 +48,6 @@ __device__ __forceinline__ void store_val(const StepArgs &a, T *cout, int s, int
     else if (a.sround) rd_st_sr(cout, idx, r, sr_species(h, s));
     else rd_st(cout, idx, r);
 }
-// p advanced by a 32-bit byte offset: a wave-uniform base plus a zero-extended 32-bit
-// offset, the form of a global access with a scalar base and a 32-bit vector offset (no
-// 64-bit address arithmetic per access).  The offsets fit: a compact species buffer holds
-// fewer than 2^30 values, and block-layout offsets stay inside one block's slab.
-template <typename T>
-__device__ __forceinline__ T *at_byte(T *p, uint32_t off)
-{
-    return (T *)((char *)p + (uint64_t)off);
-}
-template <typename T>
-__device__ __forceinline__ const T *at_byte(const T *p, uint32_t off)
-{
-    return (const T *)((const char *)p + (uint64_t)off);
-}
-// A wave-uniform pointer pinned to scalar registers, so that the compiler keeps it as the
-// scalar base of the accesses above instead of folding it into each 64-bit vector address.
-// (The field buffers are device memory: the pointer is rebuilt in the global address
-// space, so the accesses stay global ones.)
-template <typename T>
-__device__ __forceinline__ T *uniform_ptr(T *p)
-{
-    typedef __attribute__((address_space(1))) T GT;
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (T *)(GT *)(((uint64_t)hi << 32) | lo);
-}
-
 // The same with the rounding mode fixed at compile time (SR: stochastic rounding on).
 template <typename T, bool PLAIN, bool SR>
 __device__ __forceinline__ void store_val_ct(T *cout, int s, int64_t idx, uint32_t h, float r)
@@ -363,17 +335,6 @@ __global__ __launch_bounds__(256) void k_step8(StepArgs a)
 // neighbour in that direction is active (shifts of the plane word inside the block, the
 // neighbours' face words across its faces); three full adders sum the six words
 // bit-sliced, and lane l's count is bit l of the three sums.
-__device__ __forceinline__ uint64_t transpose8x8(uint64_t x)
-{
-    // bit r*8+c -> bit c*8+r: delta swaps of 1x1, 2x2 and 4x4 sub-blocks
-    uint64_t t = (x ^ (x >> 7)) & 0x00AA00AA00AA00AAull;
-    x = x ^ t ^ (t << 7);
-    t = (x ^ (x >> 14)) & 0x0000CCCC0000CCCCull;
-    x = x ^ t ^ (t << 14);
-    t = (x ^ (x >> 28)) & 0x00000000F0F0F0F0ull;
-    x = x ^ t ^ (t << 28);
-    return x;
-}
 __device__ __forceinline__ void full_add64(uint64_t a, uint64_t b, uint64_t c, uint64_t &sum, uint64_t &carry)
 {
     const uint64_t t = a ^ b;

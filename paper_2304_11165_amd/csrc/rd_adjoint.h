@@ -9,8 +9,10 @@ struct AdjArgs {
     const BlockInfo *info;
     const uint64_t *mask;
     const uint8_t *code;  // per-slot neighbour codes (bits 0-5 neighbours, bit 6 active)
+    const uint32_t *ncnt; // B = 8: active-neighbour counts per (block, lane), as in StepArgs
     const GeomInfo *geom;
     int nb;
+    int order;            // B = 8 column kernels: order of the workgroups (rd_xcd_order)
     SpeciesCoef coef;     // forward coefficients of the species (K unused)
     const float *lam_in;  // lambda^{n+1}, FP32 block-major
     float *lam_out;       // lambda^n

@@ -138,6 +138,35 @@ __device__ __forceinline__ uint64_t sector_lanes(uint64_t W)
     }
 }
 
+// ---- addressing -----------------------------------------------------------------
+// p advanced by a 32-bit byte offset: a wave-uniform base plus a zero-extended 32-bit
+// offset, the form of a global access with a scalar base and a 32-bit vector offset (no
+// 64-bit address arithmetic per access).  The offsets fit: a compact species buffer holds
+// fewer than 2^30 values, and block-layout offsets stay inside one block's slab.
+template <typename T>
+__device__ __forceinline__ T *at_byte(T *p, uint32_t off)
+{
+    return (T *)((char *)p + (uint64_t)off);
+}
+template <typename T>
+__device__ __forceinline__ const T *at_byte(const T *p, uint32_t off)
+{
+    return (const T *)((const char *)p + (uint64_t)off);
+}
+// A wave-uniform pointer pinned to scalar registers, so that the compiler keeps it as the
+// scalar base of the accesses above instead of folding it into each 64-bit vector address.
+// (The field buffers are device memory: the pointer is rebuilt in the global address
+// space, so the accesses stay global ones.)
+template <typename T>
+__device__ __forceinline__ T *uniform_ptr(T *p)
+{
+    typedef __attribute__((address_space(1))) T GT;
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (T *)(GT *)(((uint64_t)hi << 32) | lo);
+}
+
 // ---- stochastic rounding --------------------------------------------------
 // 32-bit finaliser of MurmurHash3 (Appleby): a bijective avalanche mix, used as
 // a counter-based generator keyed by (slot, species, step, seed).
@@ -502,6 +531,50 @@ __device__ __forceinline__ void stage_tile(float (*tile)[Blk<B>::TL], const T *c
             tile[s][tix] = n >= 0 ? rd_ld(c, s * sstride + (int64_t)n * K::NS + nslot) : 0.0f;
     }
 }
+
+// ---- activity of the neighbours, as lane masks (B = 8 column kernels) ------------
+// Bit r * 8 + c of x at bit c * 8 + r.
+__device__ __forceinline__ uint64_t transpose8x8(uint64_t x)
+{
+    // bit r*8+c -> bit c*8+r: delta swaps of 1x1, 2x2 and 4x4 sub-blocks
+    uint64_t t = (x ^ (x >> 7)) & 0x00AA00AA00AA00AAull;
+    x = x ^ t ^ (t << 7);
+    t = (x ^ (x >> 14)) & 0x0000CCCC0000CCCCull;
+    x = x ^ t ^ (t << 14);
+    t = (x ^ (x >> 28)) & 0x00000000F0F0F0F0ull;
+    x = x ^ t ^ (t << 28);
+    return x;
+}
+// The mask record of a block in scalar registers; the -x / +x face words also transposed
+// (bit y * 8 + z).
+struct BlockMasks {
+    uint64_t Wo[8], Wf[6], tx0, tx1;
+    __device__ __forceinline__ void load(const uint64_t *rec)
+    {
+#pragma unroll
+        for (int z = 0; z < 8; ++z) Wo[z] = rec[z];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) Wf[f] = rec[8 + f];
+        tx0 = transpose8x8(Wf[0]);
+        tx1 = transpose8x8(Wf[1]);
+    }
+    // the active lanes of plane z whose neighbour in direction d (-x, +x, -y, +y, -z, +z) is
+    // active too.  On the scalar unit; the vector unit then needs one select per neighbour
+    // where testing code bits takes three instructions.
+    __device__ __forceinline__ uint64_t pair(int z, int d) const
+    {
+        constexpr uint64_t COL0 = 0x0101010101010101ull;  // lanes with x = 0
+        const uint64_t P = Wo[z];
+        switch (d) {
+        case 0: return P & (((P << 1) & ~COL0) | ((tx0 >> z) & COL0));
+        case 1: return P & (((P >> 1) & ~(COL0 << 7)) | (((tx1 >> z) & COL0) << 7));
+        case 2: return P & ((P << 8) | ((Wf[2] >> (8 * z)) & 0xffull));
+        case 3: return P & ((P >> 8) | (((Wf[3] >> (8 * z)) & 0xffull) << 56));
+        case 4: return P & (z > 0 ? Wo[z > 0 ? z - 1 : 0] : Wf[4]);
+        default: return P & (z < 7 ? Wo[z < 7 ? z + 1 : 7] : Wf[5]);
+        }
+    }
+};
 
 // Wave-level FP64 sum in a fixed butterfly order (deterministic): partners 32, 16, 8, 4, 2
 // and 1 lanes away.  All 64 lanes must be active.  The half and row swaps and the row

@@ -766,7 +766,9 @@ static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode,
     a.mask = (const uint64_t *)(ws + sim->L.mask);
     a.code = (const uint8_t *)(ws + sim->L.code);
     a.geom = (const GeomInfo *)(ws + sim->L.geom);
+    a.ncnt = B == 8 ? (const uint32_t *)(ws + sim->L.ncnt) : nullptr;
     a.nb = nb;
+    a.order = rd_xcd_order((nb + 3) / 4, false);
     const StepArgs fa = sim->step_args(dt, sim->cur);
     a.coef = fa.coef[0];
     a.seed = seed;
@@ -799,7 +801,7 @@ static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode,
             sim->launch_shape(sa);
             if (fac) {  // the inhomogeneous step, as rd_sim_step runs it
                 const int column = B == 8 && sim->kernel != 0 ? 1 : 0;
-                sa.xcd_chunk = 0;
+                sa.xcd_chunk = column ? rd_xcd_order((nb + 3) / 4, sim->xcd_map) : 0;
                 DiffArgs da{sa, efac, {0.0f, 0.0f, 0.0f, 0.0f}};
                 LAUNCHCHK(rd_launch_step_diff(st, B, da, column, stream));
             } else {
