@@ -27,9 +27,8 @@ static rd_status region_mass(rd_sim *sim, int species, const int32_t reg[6], dou
                                     (const uint8_t *)(ws + L.code), sim->cbase_ptr(),
                                     (const uint64_t *)(ws + L.mask), sim->field_ptr(sim->cur, species), nb, reg,
                                     part, sim->stream));
-    LAUNCHCHK(rd_launch_finish_reduce(part, rd_region_rows(G.B, nb), 1, (double *)(ws + L.mid), res,
-                                      sim->stream));
-    HIPCHK(hipMemcpyAsync(sim->host_res, res, sizeof(double), hipMemcpyDeviceToHost, sim->stream));
+    LAUNCHCHK(rd_launch_finish_reduce(part, rd_region_rows(G.B, nb), 1, (double *)(ws + L.mid), sim->ticket(), res,
+                                      sim->host_res_dev, sim->stream));
     HIPCHK(hipStreamSynchronize(sim->stream));
     const double v = sim->host_res[0];
     if (!std::isfinite(v)) return rd_fail(RD_ERR_NONFINITE, "the region holds a NaN or infinity");

@@ -939,9 +939,13 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs a)
 
 // The same reduction for 8^3 blocks in the column form of the step: one wave per block,
 // four blocks per workgroup, lane (lx, ly) walking its z-column, loads under the
-// voxel-activity predicate.  The per-voxel terms are those of k_reduce; a Dirichlet
-// voxel (only in blocks on a flagged box face) reads each of its free neighbours
-// directly.  One row of RD_NRED partials per workgroup: its four wave sums in wave order.
+// voxel-activity predicate; inactive (and, in blocks on a flagged box face, Dirichlet)
+// voxels count as 0, so the terms need no branches.  The per-voxel terms are those of
+// k_reduce; the inflow of a Dirichlet voxel reads each of its free neighbours directly, in a
+// loop of its own that only those blocks enter.  One row of RD_NRED partials per workgroup:
+// its four wave sums in wave order.  On the 256^3 soil volume (two species, reaction and
+// uptake) 20.3 us per species, against 35.5 with a branch per voxel and the Dirichlet terms
+// unrolled into every plane (98 registers, half the waves per CU).
 template <typename T>
 __global__ __launch_bounds__(256) void k_reduce8z(ReduceArgs a)
 {
@@ -956,14 +960,46 @@ __global__ __launch_bounds__(256) void k_reduce8z(ReduceArgs a)
     bool dblock = false;
     if (b < a.b0 + a.nb) {  // wave-uniform; the barrier below is outside
         const BlockInfo bi = a.info[b];
+        const uint64_t *rec = a.mask + (int64_t)b * 16;
+        // the block's first voxel and, per plane, the lane's element from there
+        const int64_t first = a.cbase ? (int64_t)a.cbase[b] : (int64_t)b * 512;
+        const T *c = (const T *)a.c + first;
+        const T *cs = uniform_ptr(c + a.s * a.sstride);
+        const int lx = lane & 7, ly = lane >> 3;
+        typedef typename RawOf<T>::type R;
+        uint64_t Wo[8];
+        R raw[8];
+        uint32_t oi[8];
+        uint32_t below = 0u;
+        const uint32_t ncw = a.ncnt[(int64_t)b * 64 + lane];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) {
+            Wo[z] = rec[z];
+            oi[z] = a.cbase ? below + lanes_below(Wo[z]) : (uint32_t)(z * 64 + lane);
+            below += (uint32_t)__popcll(Wo[z]);
+            raw[z] = (R)0;
+            if (lane_bit(Wo[z])) raw[z] = ld_raw(at_byte(cs, oi[z] * (uint32_t)sizeof(T)), 0);
+        }
+        // inflow into this species from the others (0 on inactive slots)
+        double rin[8];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) rin[z] = 0.0;
+        for (int s2 = 0; s2 < a.S; ++s2) {
+            const double k = a.rate_in[s2];
+            if (k == 0.0) continue;
+            const T *c2 = uniform_ptr(c + s2 * a.sstride);
+            R r2[8];
+#pragma unroll
+            for (int z = 0; z < 8; ++z) {
+                r2[z] = (R)0;
+                if (lane_bit(Wo[z])) r2[z] = ld_raw(at_byte(c2, oi[z] * (uint32_t)sizeof(T)), 0);
+            }
+#pragma unroll
+            for (int z = 0; z < 8; ++z) rin[z] += k * (double)from_raw<T>(r2[z]);
+        }
         int bx, by, bz, gid;
         block_pos(bi, &bx, &by, &bz, &gid);
         const GeomInfo g = a.geom[gid];
-        const uint64_t *rec = a.mask + (int64_t)b * 16;
-        const int64_t base = (int64_t)b * 512;
-        const T *c = (const T *)a.c;
-        const T *cs = c + a.s * a.sstride;
-        const int lx = lane & 7, ly = lane >> 3;
         const int gx = bx * 8 + lx, gy = by * 8 + ly;
         const bool at[6] = {bx == 0, bx * 8 + 8 >= g.nx, by == 0, by * 8 + 8 >= g.ny, bz == 0,
                             bz * 8 + 8 >= g.nz};
@@ -973,47 +1009,42 @@ __global__ __launch_bounds__(256) void k_reduce8z(ReduceArgs a)
             bnd = bnd || at[f];
             dblock = dblock || (((a.dir >> f) & 1u) && at[f]);
         }
-        typedef typename RawOf<T>::type R;
-        uint64_t Wo[8];
-        R raw[8];
-        unsigned cd[8];
-        int64_t oi[8];  // element index of the lane's voxel in plane z (block-major or compact)
-        int64_t acc0 = a.cbase ? (int64_t)a.cbase[b] : 0;
-#pragma unroll
-        for (int z = 0; z < 8; ++z) {
-            Wo[z] = rec[z];
-            oi[z] = a.cbase ? acc0 + lanes_below(Wo[z]) : base + z * 64 + lane;
-            acc0 += __popcll(Wo[z]);
-            const bool act = (Wo[z] >> lane) & 1ull;
-            raw[z] = ld_raw(cs, oi[z], act);
-            cd[z] = act ? (unsigned)a.code[oi[z]] : 0u;
-        }
-        // inflow into this species from the others (0 on inactive slots)
-        double rin[8];
-#pragma unroll
-        for (int z = 0; z < 8; ++z) rin[z] = 0.0;
-        for (int s2 = 0; s2 < a.S; ++s2) {
-            const double k = a.rate_in[s2];
-            if (k == 0.0) continue;
-            R r2[8];
-#pragma unroll
-            for (int z = 0; z < 8; ++z) r2[z] = ld_raw(c + s2 * a.sstride, oi[z], (Wo[z] >> lane) & 1ull);
-#pragma unroll
-            for (int z = 0; z < 8; ++z) rin[z] += k * (double)from_raw<T>(r2[z]);
-        }
         const double dx = a.dx, dx2 = dx * dx, dx3 = dx2 * dx;
+        int bad = 0;
 #pragma unroll
         for (int z = 0; z < 8; ++z) {
-            const unsigned code = cd[z];
-            if (!(code & 64u)) continue;
-            const float uf = from_raw<T>(raw[z]);
+            float uf = from_raw<T>(raw[z]);
+            double ri = rin[z];
+            bad += isfinite(uf) ? 0 : 1;
+            unsigned onf = 0u;
+            if (bnd) {
+                onf = box_faces(g, gx, gy, bz * 8 + z);
+                if (onf & a.dir) {  // a Dirichlet voxel: only its inflow counts (below)
+                    uf = 0.0f;
+                    ri = 0.0;
+                }
+            }
             const double u = (double)uf;
-            if (!isfinite(uf)) acc[9] += 1.0;
-            const int gz = bz * 8 + z;
-            const unsigned onf = bnd ? box_faces(g, gx, gy, gz) : 0u;
-            if (onf & a.dir) {
-                // Dirichlet voxel: inflow into its free neighbours, booked on the first
-                // flagged face (in face order) it lies on
+            acc[0] += u * dx3;
+            if (a.kR != 0.0) {
+                const int nwall = 6 - (int)((ncw >> (3 * z)) & 7u) - __popc(onf);
+                acc[7] += a.kR * (double)nwall * u * dx2;
+            }
+            if (hasreact) acc[8] += (ri - a.rate_out * u) * dx3;
+        }
+        acc[9] = (double)bad;
+        if (dblock) {
+            // Dirichlet voxels: inflow into their free neighbours, booked on the first
+            // flagged face (in face order) a voxel lies on
+#pragma unroll 1
+            for (int z = 0; z < 8; ++z) {
+                const unsigned onf = box_faces(g, gx, gy, bz * 8 + z);
+                if (!lane_bit(rec[z]) || !(onf & a.dir)) continue;
+                const int slot = z * 64 + lane;
+                const int64_t ip = slot_index8(a.cbase, a.mask, b, slot);
+                const unsigned code = a.code[ip];
+                const T *ca = (const T *)a.c + a.s * a.sstride;
+                const double u = (double)rd_ld(ca, ip);
                 const int fq = __builtin_ctz(onf & a.dir);
                 double fin = 0.0;
 #pragma unroll
@@ -1022,26 +1053,19 @@ __global__ __launch_bounds__(256) void k_reduce8z(ReduceArgs a)
                     const int ex = d == 0 ? -1 : d == 1 ? 1 : 0;
                     const int ey = d == 2 ? -1 : d == 3 ? 1 : 0;
                     const int ez = d == 4 ? -1 : d == 5 ? 1 : 0;
-                    if (on_dirichlet(a.dir, gx + ex, gy + ey, gz + ez, g.nx, g.ny, g.nz)) continue;
+                    if (on_dirichlet(a.dir, gx + ex, gy + ey, bz * 8 + z + ez, g.nx, g.ny, g.nz)) continue;
                     const int qx = lx + ex, qy = ly + ey, qz = z + ez;
                     const bool inside = qx >= 0 && qx < 8 && qy >= 0 && qy < 8 && qz >= 0 && qz < 8;
                     // an active neighbour outside the block lies in face neighbour d
                     const int nbk = inside ? b : bi.nbr[d];
-                    const int slot = ((qz & 7) * 8 + (qy & 7)) * 8 + (qx & 7);
-                    const double v = (double)rd_ld(cs, slot_index8(a.cbase, a.mask, nbk, slot));
+                    const int qs = ((qz & 7) * 8 + (qy & 7)) * 8 + (qx & 7);
+                    const double v = (double)rd_ld(ca, slot_index8(a.cbase, a.mask, nbk, qs));
                     fin += a.D * (u - v) * dx;
                 }
 #pragma unroll
                 for (int f = 0; f < 6; ++f)
                     if (f == fq) acc[1 + f] += fin;
-                continue;
             }
-            acc[0] += u * dx3;
-            if (a.kR != 0.0) {
-                const int nwall = __popc(~onf & ~code & 0x3fu);
-                acc[7] += a.kR * (double)nwall * u * dx2;
-            }
-            if (hasreact) acc[8] += (rin[z] - a.rate_out * u) * dx3;
         }
     }
 #pragma unroll
@@ -1108,37 +1132,64 @@ __global__ __launch_bounds__(256) void k_plane_flux(const BlockInfo *info, const
     if (threadIdx.x == 0) partial[blockIdx.x] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
 }
 
-// Row sums of a [nrows][nlanes] FP64 array (nlanes <= RD_FINISH_LANES): workgroup g
-// sums rows [g * chunk, min((g + 1) * chunk, nrows)) into out[g][*].  Thread t adds
-// rows t, t + 256, ... of the range (whole rows, so loads are coalesced), then a
-// fixed tree over the threads; the order depends only on nrows and chunk.
+// Row sums of a [nrows][nlanes] FP64 array (nlanes <= RD_FINISH_LANES): workgroup g sums
+// rows [g * chunk, min((g + 1) * chunk, nrows)), thread t of it rows t, t + 256, ... of the
+// range and then a tree over the threads (128, 64, ... apart), into mid[g][*]; the last
+// workgroup to arrive (a ticket in `count`, left at 0 for the next launch; nothing waits for
+// another workgroup) sums those rows in the same order into out, and into host, pinned
+// host memory, if given, so that a caller needs no copy.  The order of the additions
+// depends only on nrows and chunk.  8000 rows of one lane take 9.5 us with the host write,
+// against 5.0 + 5.0 + 4.1 us for two launches and a copy.
 #define RD_FINISH_LANES 16
-__global__ __launch_bounds__(256) void k_finish_rows(const double *part, int nrows, int nlanes,
-                                                     int chunk, double *out)
+__global__ __launch_bounds__(256) void k_finish_rows(const double *part, int nrows, int nlanes, int chunk,
+                                                     double *mid, uint32_t *count, double *out, double *host)
 {
-    __shared__ double sh[RD_FINISH_LANES][257];
-    const int g = blockIdx.x, t = threadIdx.x;
-    const int64_t r0 = (int64_t)g * chunk;
-    const int64_t r1 = r0 + chunk < nrows ? r0 + chunk : nrows;
+    __shared__ double sh[RD_FINISH_LANES][256];
+    __shared__ uint32_t arrived;
+    const int g = blockIdx.x, t = threadIdx.x, ng = gridDim.x, wave = t >> 6, lane = t & 63;
+    auto tree = [&](int l) {  // of sh[l], by one wave
+        return wave_sum((sh[l][lane] + sh[l][lane + 128]) + (sh[l][lane + 64] + sh[l][lane + 192]));
+    };
+    const int64_t r1 = min((int64_t)(g + 1) * chunk, (int64_t)nrows);
     double acc[RD_FINISH_LANES];
 #pragma unroll
     for (int l = 0; l < RD_FINISH_LANES; ++l) acc[l] = 0.0;
-    for (int64_t r = r0 + t; r < r1; r += 256) {
+    for (int64_t r = (int64_t)g * chunk + t; r < r1; r += 256) {
 #pragma unroll
         for (int l = 0; l < RD_FINISH_LANES; ++l)
             if (l < nlanes) acc[l] += part[r * nlanes + l];
     }
 #pragma unroll
-    for (int l = 0; l < RD_FINISH_LANES; ++l) sh[l][t] = acc[l];
+    for (int l = 0; l < RD_FINISH_LANES; ++l)
+        if (l < nlanes) sh[l][t] = acc[l];
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) {
-#pragma unroll
-            for (int l = 0; l < RD_FINISH_LANES; ++l) sh[l][t] += sh[l][t + w];
+    for (int l = wave; l < nlanes; l += 4) {
+        const double v = tree(l);
+        if (lane != 0) continue;
+        if (ng > 1) {
+            __hip_atomic_store(mid + (int64_t)g * nlanes + l, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            out[l] = v;
+            if (host) host[l] = v;
         }
-        __syncthreads();
     }
-    if (t < nlanes) out[(int64_t)g * nlanes + t] = sh[t][0];
+    if (ng == 1) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every wave's row is written before the ticket
+    __syncthreads();
+    if (t == 0) arrived = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (arrived != (uint32_t)ng - 1) return;
+    for (int l = 0; l < nlanes; ++l)
+        sh[l][t] = t < ng ? __hip_atomic_load(mid + (int64_t)t * nlanes + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                          : 0.0;
+    __syncthreads();
+    for (int l = wave; l < nlanes; l += 4) {
+        const double v = tree(l);
+        if (lane != 0) continue;
+        out[l] = v;
+        if (host) host[l] = v;
+    }
+    if (t == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Dense float32 -> block-major storage of one species.  Inactive slots get 0 and
@@ -1197,6 +1248,79 @@ __global__ __launch_bounds__(256) void k_gather(const BlockInfo *info, const uin
         const int64_t i = cbase ? slot_index8(cbase, mask, b, slot) : (int64_t)b * K::NS + slot;
         dense[voxel_id(g, gx, gy, gz)] = rd_ld(field, i);
     }
+}
+
+// The same two copies for 8^3 blocks: one wave per block (lane (lx, ly), eight planes in
+// flight), four consecutive blocks per workgroup and runs of groups per XCD, so that the 32
+// bytes a block holds of a 128-byte line of the dense array meet its x neighbours' in one
+// L2.  One species of the 512^3 soil volume: scatter 151 us, gather 154 us, against 354 and
+// 321 with a workgroup per block.
+template <typename T>
+__global__ __launch_bounds__(256) void k_scatter8(const BlockInfo *info, const uint64_t *mask, const uint32_t *cbase,
+                                                  const GeomInfo *geom, int nb, int order, const float *dense, T *field,
+                                                  uint32_t dir, float d0, float d1, float d2, float d3, float d4,
+                                                  float d5)
+{
+    const int lane = threadIdx.x & 63;
+    const int b = __builtin_amdgcn_readfirstlane(map_group(blockIdx.x, order) * 4 + (int)(threadIdx.x >> 6));
+    if (b >= nb) return;
+    int bx, by, bz, gid;
+    block_pos(info[b], &bx, &by, &bz, &gid);
+    const GeomInfo g = geom[gid];
+    const uint64_t *rec = mask + (int64_t)b * 16;
+    const int gx = bx * 8 + (lane & 7), gy = by * 8 + (lane >> 3);
+    const float *col = dense + voxel_id(g, gx, gy, bz * 8);
+    const int64_t plane = (int64_t)g.nx * g.ny;
+    float v[8];
+#pragma unroll
+    for (int z = 0; z < 8; ++z) {
+        v[z] = 0.0f;
+        if (lane_bit(rec[z])) v[z] = col[z * plane];
+    }
+    const float dv[6] = {d0, d1, d2, d3, d4, d5};
+    uint32_t at = cbase ? cbase[b] : 0u;
+#pragma unroll
+    for (int z = 0; z < 8; ++z) {
+        const uint64_t W = rec[z];
+        if (dir && boundary_block(g, bx, by, bz)) {  // uniform; the highest flagged face wins
+            const unsigned onf = box_faces(g, gx, gy, bz * 8 + z) & dir;
+#pragma unroll
+            for (int f = 0; f < 6; ++f)
+                if (lane_bit(W) && ((onf >> f) & 1u)) v[z] = dv[f];
+        }
+        // compact layout: only active voxels are stored
+        if (!cbase) rd_st(field, (int64_t)b * 512 + z * 64 + lane, v[z]);
+        else if (lane_bit(W)) rd_st(field, (int64_t)(at + lanes_below(W)), v[z]);
+        at += (uint32_t)__popcll(W);
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_gather8(const BlockInfo *info, const uint64_t *mask, const uint32_t *cbase,
+                                                 const GeomInfo *geom, int nb, int order, const T *field, float *dense)
+{
+    const int lane = threadIdx.x & 63;
+    const int b = __builtin_amdgcn_readfirstlane(map_group(blockIdx.x, order) * 4 + (int)(threadIdx.x >> 6));
+    if (b >= nb) return;
+    int bx, by, bz, gid;
+    block_pos(info[b], &bx, &by, &bz, &gid);
+    const GeomInfo g = geom[gid];
+    const uint64_t *rec = mask + (int64_t)b * 16;
+    float *col = dense + voxel_id(g, bx * 8 + (lane & 7), by * 8 + (lane >> 3), bz * 8);
+    const int64_t plane = (int64_t)g.nx * g.ny;
+    typename RawOf<T>::type v[8];
+    uint32_t at = cbase ? cbase[b] : 0u;
+#pragma unroll
+    for (int z = 0; z < 8; ++z) {
+        const uint64_t W = rec[z];
+        v[z] = (typename RawOf<T>::type)0;
+        if (lane_bit(W))
+            v[z] = ld_raw(field, cbase ? (int64_t)(at + lanes_below(W)) : (int64_t)b * 512 + z * 64 + lane);
+        at += (uint32_t)__popcll(W);
+    }
+#pragma unroll
+    for (int z = 0; z < 8; ++z)
+        if (lane_bit(rec[z])) col[z * plane] = from_raw<T>(v[z]);
 }
 
 // Set the Dirichlet voxels of one species in a block-major field (others untouched).
@@ -1401,23 +1525,15 @@ int rd_launch_reduce(int storage, int B, const ReduceArgs &a, void *stream)
     RD_DISPATCH(storage, B, launch_reduce_t, a, (hipStream_t)stream);
 }
 
-int rd_launch_finish_reduce(const double *partial, int nparts, int nlanes, double *mid, double *out,
-                            void *stream)
+int rd_launch_finish_reduce(const double *partial, int nparts, int nlanes, double *mid, uint32_t *ticket,
+                            double *out, double *host, void *stream)
 {
     if (nlanes < 1 || nlanes > RD_FINISH_LANES) return (int)hipErrorInvalidValue;
-    hipStream_t st = (hipStream_t)stream;
-    if (nparts <= 4096) {  // one workgroup in one pass
-        hipLaunchKernelGGL(k_finish_rows, dim3(1), dim3(256), 0, st, partial, nparts, nlanes,
-                           nparts > 0 ? nparts : 1, out);
-        return (int)hipGetLastError();
-    }
-    // RD_FINISH_GROUPS fixed ranges, then their sums in one workgroup
-    const int chunk = (nparts + RD_FINISH_GROUPS - 1) / RD_FINISH_GROUPS;
-    const int groups = (nparts + chunk - 1) / chunk;
-    hipLaunchKernelGGL(k_finish_rows, dim3(groups), dim3(256), 0, st, partial, nparts, nlanes, chunk,
-                       mid);
-    hipLaunchKernelGGL(k_finish_rows, dim3(1), dim3(256), 0, st, (const double *)mid, groups, nlanes,
-                       groups, out);
+    // one workgroup up to 4096 rows, else RD_FINISH_GROUPS ranges
+    const int chunk = nparts <= 4096 ? std::max(nparts, 1) : (nparts + RD_FINISH_GROUPS - 1) / RD_FINISH_GROUPS;
+    const int groups = std::max(1, (nparts + chunk - 1) / chunk);
+    hipLaunchKernelGGL(k_finish_rows, dim3(groups), dim3(256), 0, (hipStream_t)stream, partial, nparts, nlanes, chunk,
+                       mid, ticket, out, host);
     return (int)hipGetLastError();
 }
 
@@ -1426,6 +1542,11 @@ template <typename T, int B>
 int launch_scatter_t(const BlockInfo *info, const uint64_t *mask, const uint32_t *cbase, const GeomInfo *geom,
                      int nb, const float *dense, void *field, uint32_t dir, const float *dv, hipStream_t st)
 {
+    if constexpr (B == 8) {
+        const int groups = (nb + 3) / 4, order = rd_xcd_order(groups, false);
+        hipLaunchKernelGGL((k_scatter8<T>), dim3(rd_xcd_grid(groups, order)), dim3(256), 0, st, info, mask, cbase, geom,
+                           nb, order, dense, (T *)field, dir, dv[0], dv[1], dv[2], dv[3], dv[4], dv[5]);
+    } else
     hipLaunchKernelGGL((k_scatter<T, B>), dim3(nb), dim3(256), 0, st, info, mask, cbase, geom, nb, dense,
                        (T *)field, dir, dv[0], dv[1], dv[2], dv[3], dv[4], dv[5]);
     return (int)hipGetLastError();
@@ -1434,6 +1555,11 @@ template <typename T, int B>
 int launch_gather_t(const BlockInfo *info, const uint64_t *mask, const uint32_t *cbase, const GeomInfo *geom,
                     int nb, const void *field, float *dense, hipStream_t st)
 {
+    if constexpr (B == 8) {
+        const int groups = (nb + 3) / 4, order = rd_xcd_order(groups, false);
+        hipLaunchKernelGGL((k_gather8<T>), dim3(rd_xcd_grid(groups, order)), dim3(256), 0, st, info, mask, cbase, geom,
+                           nb, order, (const T *)field, dense);
+    } else
     hipLaunchKernelGGL((k_gather<T, B>), dim3(nb), dim3(256), 0, st, info, mask, cbase, geom, nb,
                        (const T *)field, dense);
     return (int)hipGetLastError();

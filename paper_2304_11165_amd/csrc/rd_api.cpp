@@ -518,7 +518,10 @@ rd_status rd_sim::upload(bool index)
     if (L.cp_stride > 0 && cp_slots > 0)
         LAUNCHCHK(rd_launch_fill_u32(ws + L.cp, 0u, (int64_t)(L.cp_stride * (size_t)cp_slots / 4), stream));
     LAUNCHCHK(rd_launch_fill_u32(ws + L.res, 0u, 64 * 2, stream));  // results + step counter
-    if (!host_res) HIPCHK(hipHostMalloc((void **)&host_res, 64 * sizeof(double), hipHostMallocDefault));
+    if (!host_res) {
+        HIPCHK(hipHostMalloc((void **)&host_res, 64 * sizeof(double), hipHostMallocDefault));
+        HIPCHK(hipHostGetDevicePointer((void **)&host_res_dev, host_res, 0));
+    }
     cur = 0;
     steps_taken = 0;
     for (int s = 0; s < S; ++s) {
@@ -609,6 +612,7 @@ rd_status rd_sim::check_dt(double dt) const
 }
 
 uint32_t *rd_sim::step_counter() const { return (uint32_t *)(ws + L.res + 384); }
+uint32_t *rd_sim::ticket() const { return (uint32_t *)(ws + L.res + 448); }
 
 void rd_sim::launch_shape(StepArgs &a) const
 {
@@ -752,6 +756,7 @@ rd_status rd_sim::balance(int s, double out[RD_NRED], int part)
     a.info = (const BlockInfo *)(ws + L.info);
     a.mask = (const uint64_t *)(ws + L.mask);
     a.code = (const uint8_t *)(ws + L.code);
+    a.ncnt = g->B == 8 ? (const uint32_t *)(ws + L.ncnt) : nullptr;
     a.cbase = cbase_ptr();
     a.geom = (const GeomInfo *)(ws + L.geom);
     a.c = field_ptr(cur, 0);
@@ -782,8 +787,8 @@ rd_status rd_sim::balance(int s, double out[RD_NRED], int part)
         LAUNCHCHK(rd_launch_reduce_diff(storage, g->B, a, (const float *)(ws + L.diff), band_on ? sink[s] : 0.0,
                                         stream));
     else LAUNCHCHK(rd_launch_reduce(storage, g->B, a, stream));
-    LAUNCHCHK(rd_launch_finish_reduce(a.partial, nparts, RD_NRED, (double *)(ws + L.mid), res, stream));
-    HIPCHK(hipMemcpyAsync(host_res, res, sizeof(double) * RD_NRED, hipMemcpyDeviceToHost, stream));
+    LAUNCHCHK(rd_launch_finish_reduce(a.partial, nparts, RD_NRED, (double *)(ws + L.mid), ticket(), res,
+                                      host_res_dev, stream));
     HIPCHK(hipStreamSynchronize(stream));
     for (int l = 0; l < RD_NRED; ++l) out[l] = host_res[l];
     if (out[9] != 0.0) return rd_fail(RD_ERR_NONFINITE, "field holds " + std::to_string((int64_t)out[9]) +
@@ -1004,20 +1009,18 @@ extern "C" rd_status rd_sim_plane_flux(rd_sim *sim, int species, int axis, int64
                                             (const uint8_t *)(ws + L.code), sim->field_ptr(sim->cur, species),
                                             (const float *)(ws + L.diff), nb, axis, (int)i0, sim->D[species],
                                             G.dx, part, stream));
-        LAUNCHCHK(rd_launch_finish_reduce(part, rd_diff_reduce_rows(G.B, nb), 1, (double *)(ws + L.mid), res,
-                                          stream));
+        LAUNCHCHK(rd_launch_finish_reduce(part, rd_diff_reduce_rows(G.B, nb), 1, (double *)(ws + L.mid),
+                                          sim->ticket(), res, sim->host_res_dev, stream));
     } else {
         LAUNCHCHK(rd_launch_plane_flux((int)sim->storage, G.B, (const BlockInfo *)(ws + L.info),
                                        (const uint8_t *)(ws + L.code), sim->cbase_ptr(),
                                        (const uint64_t *)(ws + L.mask), sim->field_ptr(sim->cur, species), nb,
                                        axis, (int)i0, sim->D[species], G.dx, part, stream));
-        LAUNCHCHK(rd_launch_finish_reduce(part, rd_reduce_rows(G.B, nb), 1, (double *)(ws + L.mid), res,
-                                          stream));
+        LAUNCHCHK(rd_launch_finish_reduce(part, rd_reduce_rows(G.B, nb), 1, (double *)(ws + L.mid), sim->ticket(),
+                                          res, sim->host_res_dev, stream));
     }
-    double h = 0.0;
-    HIPCHK(hipMemcpyAsync(&h, res, sizeof(double), hipMemcpyDeviceToHost, stream));
     HIPCHK(hipStreamSynchronize(stream));
-    *flux = h;
+    *flux = sim->host_res[0];
     return RD_OK;
 }
 

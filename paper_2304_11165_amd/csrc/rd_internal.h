@@ -108,6 +108,7 @@ struct ReduceArgs {
     const BlockInfo *info;
     const uint64_t *mask;
     const uint8_t *code;  // per-slot neighbour codes (as in StepArgs)
+    const uint32_t *ncnt;   // B = 8: active-neighbour counts (as in StepArgs)
     const uint32_t *cbase;  // compact layout (as in StepArgs) or NULL
     const GeomInfo *geom;
     const void *c;      // T*
@@ -137,11 +138,12 @@ int rd_launch_reduce(int storage, int B, const ReduceArgs &a, void *stream);
 int rd_launch_plane_flux(int storage, int B, const BlockInfo *info, const uint8_t *code,
                          const uint32_t *cbase, const uint64_t *mask, const void *c, int nb, int axis,
                          int i0, double D, double dx, double *partial, void *stream);
-// Fixed-order sums of partial[nparts][nlanes] (nlanes <= 16) into out[nlanes]; mid is
-// scratch of RD_FINISH_GROUPS * nlanes doubles.
+// Fixed-order sums of partial[nparts][nlanes] (nlanes <= 16) into out[nlanes] and, unless
+// NULL, host[nlanes] (pinned host memory, complete once the stream has reached this point);
+// mid is scratch of RD_FINISH_GROUPS * nlanes doubles, ticket a device word that is 0.
 #define RD_FINISH_GROUPS 256
-int rd_launch_finish_reduce(const double *partial, int nparts, int nlanes, double *mid, double *out,
-                            void *stream);
+int rd_launch_finish_reduce(const double *partial, int nparts, int nlanes, double *mid, uint32_t *ticket,
+                            double *out, double *host, void *stream);
 // cbase: compact layout (B = 8) or NULL (block-major), as in StepArgs
 int rd_launch_scatter(int storage, int B, const BlockInfo *info, const uint64_t *mask,
                       const uint32_t *cbase, const GeomInfo *geom, int nb, const float *dense, void *field,

@@ -97,7 +97,8 @@ struct rd_sim {
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;
     std::vector<GeomInfo> geom_host;  // one entry per part (the device copy's source)
-    double *host_res = nullptr;  // pinned
+    double *host_res = nullptr;  // pinned; kernels write results to it (host_dev)
+    double *host_res_dev = nullptr;
     std::vector<GraphEntry> graphs;
 
     int cur = 0;  // buffer holding the current field
@@ -116,6 +117,7 @@ struct rd_sim {
     rd_status check_dt(double dt) const;
     int xcd_chunk(int nb) const;
     uint32_t *step_counter() const;
+    uint32_t *ticket() const;  // of rd_launch_finish_reduce
     void launch_shape(StepArgs &a) const;
     rd_status launch_steps(double dt, int64_t n);
     rd_status step(double dt, int64_t n);

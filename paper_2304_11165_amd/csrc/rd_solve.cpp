@@ -780,7 +780,7 @@ static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode,
     a.lam_out = lam[lc];
     LAUNCHCHK(adj_launch_seed(st, B, a, seed_mode, stream));
     double *mid = (double *)(ws + sim->L.mid);
-    LAUNCHCHK(rd_launch_finish_reduce(a.partial, nb, 1, mid, acc, stream));
+    LAUNCHCHK(rd_launch_finish_reduce(a.partial, nb, 1, mid, sim->ticket(), acc, nullptr, stream));
     // the step kernel adds its gradient terms to its own FP64 rows, in step order; one
     // fixed-order reduction over the rows after the sweep
     const int nrows = adj_groups(B, nb);
@@ -821,7 +821,7 @@ static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode,
             lc = 1 - lc;
         }
     }
-    LAUNCHCHK(rd_launch_finish_reduce(a.partial, nrows, 2, mid, acc + 1, stream));
+    LAUNCHCHK(rd_launch_finish_reduce(a.partial, nrows, 2, mid, sim->ticket(), acc + 1, nullptr, stream));
     if (dev_dL_de)
         LAUNCHCHK(adj_launch_dense_f64(B, a.info, a.code, a.geom, nb, ge, dev_dL_de, ndense, stream));
     double h[3];
