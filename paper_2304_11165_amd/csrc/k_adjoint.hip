@@ -60,7 +60,7 @@ __global__ __launch_bounds__(256) void k_adjoint(AdjArgs a)
                     const float nbv[6] = {ts[t - 1], ts[t + 1], ts[t - K::E], ts[t + K::E],
                                           ts[t - K::E * K::E], ts[t + K::E * K::E]};
                     const float cen[1] = {lp};
-                    out = rd_update<1>(lp, nbv, nbm, nwall, a.coef, cen);
+                    out = rd_update<1>(lp, nbv, nbm, nwall, a.coef, cen, 0);
                     // gradient partials with the forward state c^n
                     const float *tcs = tc[sub][0];
                     const float cc = tcs[t];
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void k_adjoint8(AdjArgs a)
         const float nbl[6] = {TL[o - 1], TL[o + 1], TL[o - 10], TL[o + 10], z == 0 ? lh[4] : lc[z > 0 ? z - 1 : 0],
                               z == 7 ? lh[5] : lc[z < 7 ? z + 1 : 7]};
         const float cen[1] = {lp};
-        float r = rd_update_n<1>(lp, nbl, nact, nwall, a.coef, cen);
+        float r = rd_update_n<1>(lp, nbl, nact, nwall, a.coef, cen, 0);
         if (bnd) {  // Dirichlet voxels lie on the box faces: boundary blocks only (uniform)
             if ((onf & a.coef.dir) != 0u) r = 0.0f;
         }

@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void k_step8l(StepArgs a)
 #pragma unroll
             for (int q = 0; q < S; ++q) cen[q] = c[q][z];
             const float dth = DTH ? fp32_dither(cz, sr_species(h, s)) : 0.0f;
-            const float upd = rd_update<S, DTH>(cz, nbv, m, nwall, a.coef[s], cen, dth);
+            const float upd = rd_update<S, DTH>(cz, nbv, m, nwall, a.coef[s], cen, s, dth);
             res[s] = (dblk && (onf & a.coef[s].dir) != 0u) ? cz : upd;
         }
 #pragma unroll

@@ -87,7 +87,7 @@ __device__ __forceinline__ void vox8(const StepArgs &a, const float *ts, int sst
         const float *p = ts + s * sstr;
         const float nbv[6] = {p[-1], p[1], p[-oy], p[oy], p[-oz], p[oz]};
         const float dth = DTH ? fp32_dither(cen[s], sr_species(hd, s)) : 0.0f;
-        const float upd = rd_update<S, DTH>(cen[s], nbv, m, nwall, a.coef[s], cen, dth);
+        const float upd = rd_update<S, DTH>(cen[s], nbv, m, nwall, a.coef[s], cen, s, dth);
         const bool isd = (onf & a.coef[s].dir) != 0u;
         out[s] = act ? (isd ? cen[s] : upd) : 0.0f;
     }
@@ -115,7 +115,7 @@ __device__ __forceinline__ void vox_code(const StepArgs &a, const float *ts, int
         const float *p = ts + s * sstr;
         const float nbv[6] = {p[-1], p[1], p[-oy], p[oy], p[-oz], p[oz]};
         const float dth = DTH ? fp32_dither(cen[s], sr_species(hd, s)) : 0.0f;
-        const float upd = rd_update<S, DTH>(cen[s], nbv, m, nwall, a.coef[s], cen, dth);
+        const float upd = rd_update<S, DTH>(cen[s], nbv, m, nwall, a.coef[s], cen, s, dth);
         const bool isd = (onf & a.coef[s].dir) != 0u;
         out[s] = act ? (isd ? cen[s] : upd) : 0.0f;
     }
@@ -571,7 +571,7 @@ __device__ __forceinline__ void step8z_group(const StepArgs &a, int grp)
         for (int s = 0; s < S; ++s) {
             float *ts = tile[wv][s];
             ts[z8::pix(lx, ly)] = c[s][z];
-            if (ly == z) {
+            if (lane_bit(0xffull << (8 * z))) {
                 ts[z8::pix(-1, lx)] = side[0][s];
                 ts[z8::pix(8, lx)] = side[1][s];
                 ts[z8::pix(lx, -1)] = side[2][s];
@@ -587,7 +587,6 @@ __device__ __forceinline__ void step8z_group(const StepArgs &a, int grp)
         // active-neighbour count; walls are the in-box neighbours that are not active
         // (out-of-box ones never are)
         const float nact = (float)((ncw >> (3 * z)) & 7u);
-        const bool act = lane_bit(Wo[z]);
         unsigned onf = 0u;
         if (bnd) onf = box_faces(g, gx, gy, gz);
         const float nwall = (6.0f - nact) - (float)__popc(onf);
@@ -602,12 +601,11 @@ __device__ __forceinline__ void step8z_group(const StepArgs &a, int grp)
             const float up = z == 7 ? zhi[s] : c[s][z < 7 ? z + 1 : 7];
             const float nbv[6] = {p[-1], p[1], p[-10], p[10], dn, up};
             const float dth = DITHER ? fp32_dither(cen[s], sr_species(h, s)) : 0.0f;
-            const float upd = rd_update_n<S, DITHER>(cen[s], nbv, nact, nwall, a.coef[s], cen, dth);
-            float r = upd;
+            float r = rd_update_n<S, DITHER>(cen[s], nbv, nact, nwall, a.coef[s], cen, s, dth);
             if (bnd) {  // Dirichlet voxels lie on the box faces: boundary blocks only (uniform)
                 if ((onf & a.coef[s].dir) != 0u) r = cen[s];
             }
-            res[s] = act ? r : 0.0f;
+            res[s] = CMP || lane_bit(Wo[z]) ? r : 0.0f;  // compact: only active lanes store
         }
         // every lane has read plane z before any lane overwrites it with plane z + 1
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

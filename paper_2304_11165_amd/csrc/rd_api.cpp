@@ -614,9 +614,23 @@ rd_status rd_sim::check_dt(double dt) const
 uint32_t *rd_sim::step_counter() const { return (uint32_t *)(ws + L.res + 384); }
 uint32_t *rd_sim::ticket() const { return (uint32_t *)(ws + L.res + 448); }
 
+// Short block lists leave most of the chip idle with a wave per block, and a wave's eight
+// planes are a serial chain: the column kernels then run as the workgroup-per-block kernel
+// (two planes per wave; same bits).  us per step in captured graphs, column / workgroup per
+// block, packings of 64^3, 80^3, 96^3 (505, 989, 1710 blocks): one species FP32 4.0 / 3.3,
+// 4.1 / 3.7, 4.4 / 4.5; two species FP32 4.8 / 3.7, 5.1 / 4.3, 5.9 / 5.4, BF16 with
+// stochastic rounding 5.6 / 4.2, 5.7 / 4.8, 6.6 / 6.1; 112^3 (2714) two species 7.0 / 6.8,
+// BF16 7.8 / 8.2.
+int rd_sim::step_kernel() const
+{
+    if (g->B != 8) return 0;
+    const bool column = kernel == 2 || kernel == 3;
+    return column && !compact && g->nb() <= (S == 1 ? 1024 : 1792) ? 0 : kernel;
+}
+
 void rd_sim::launch_shape(StepArgs &a) const
 {
-    a.kernel = g->B == 8 ? kernel : 0;
+    a.kernel = step_kernel();
     a.xcd_chunk = xcd_chunk(a.nb);
     if (a.kernel == 1) {
         // a multiple of 8 (one share per XCD), no more workgroups than blocks need
@@ -685,9 +699,9 @@ rd_status rd_sim::launch_steps(double dt, int64_t n)
 int rd_sim::xcd_chunk(int nb) const
 {
     // the persistent kernel splits the list itself (by XCD only if asked to)
-    if (g->B == 8 && kernel == 1) return xcd_map && nb >= 64 ? (nb + 7) / 8 : 0;
+    if (step_kernel() == 1) return xcd_map && nb >= 64 ? (nb + 7) / 8 : 0;
     // blocks per workgroup: 1 for the B = 8 workgroup kernel, 4 for the wave kernels
-    const int bpw = g->B == 8 && kernel == 0 ? 1 : 4;
+    const int bpw = g->B == 8 && step_kernel() == 0 ? 1 : 4;
     return rd_xcd_order((nb + bpw - 1) / bpw, xcd_map);
 }
 

@@ -26,14 +26,10 @@ __device__ __forceinline__ float rd_ld(const bf16_t *p, int64_t i)
 }
 __device__ __forceinline__ float rd_ld(const _Float16 *p, int64_t i) { return (float)p[i]; }
 
-// BF16 round to nearest even on the upper 16 bits; NaN stays NaN (quiet bit set).
-__device__ __forceinline__ uint16_t bf16_rne(float v)
-{
-    uint32_t u = __float_as_uint(v);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+// BF16 round to nearest even; NaN stays NaN (quiet bit set).  One conversion instruction
+// of gfx950, equal to adding 0x7fff + (bit 16) to the FP32 pattern and cutting its lower half
+// on all 2^32 patterns.
+__device__ __forceinline__ uint16_t bf16_rne(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
 
 // FP32 fields are streamed (written once per step, read by the next step), so their
 // stores are nontemporal (measured faster on the 512^3 soil volume).
@@ -129,6 +125,12 @@ __device__ __forceinline__ uint64_t sector_lanes(uint64_t W)
     constexpr int V = RD_STORE_SECTOR / (int)sizeof(T) < 64 ? RD_STORE_SECTOR / (int)sizeof(T) : 64;
     if constexpr (V == 64) {
         return W != 0ull ? ~0ull : 0ull;
+    } else if constexpr (V == 32) {
+        // by halves (the readfirstlane keeps them 32-bit: a compare of the 64-bit word would go
+        // to the vector unit)
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)W);
+        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(W >> 32));
+        return (uint64_t)(hi != 0u ? ~0u : 0u) << 32 | (lo != 0u ? ~0u : 0u);
     } else {
         constexpr uint64_t ONE = (1ull << V) - 1ull;
         uint64_t m = 0ull;
@@ -226,22 +228,22 @@ __device__ __forceinline__ uint32_t sr_species(uint32_t h, int species)
 __device__ __forceinline__ uint16_t bf16_sr(float v, uint32_t rnd)
 {
     // BF16 is the upper half of the FP32 pattern: 16 random bits below the cut round the
-    // magnitude up with probability (low bits) / 2^16.  Infinities keep their zero low
-    // bits' pattern above the cut; a NaN stays a (quiet) NaN.
-    const uint32_t u = __float_as_uint(v);
-    const bool nan = (u & 0x7fffffffu) > 0x7f800000u;
-    return nan ? (uint16_t)((u >> 16) | 0x40u) : (uint16_t)((u + (rnd & 0xffffu)) >> 16);
+    // magnitude up with probability (low bits) / 2^16; infinities stay, a NaN stays a (quiet)
+    // NaN.  The conversion instruction takes the 16 bits from the upper half of its operand
+    // and equals that sum on all 2^32 patterns.
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 r = __builtin_amdgcn_cvt_sr_bf16_f32(bf16x2{}, v, rnd << 16, false);
+    return __builtin_bit_cast(uint16_t, r[0]);
 }
 
-__device__ __forceinline__ _Float16 f16_sr(float v, uint32_t rnd)
+// FP16 in software: FP16 keeps 10 mantissa bits down to 2^-14 (13 FP32 bits below its cut)
+// and a fixed spacing of 2^-24 below (d = 126 - biased exponent bits below the cut, up to
+// 23); d random bits (the 16 given, shifted into the top of the d) are added to the
+// magnitude's pattern and the low d bits cleared, which leaves a multiple of the FP16
+// spacing (a carry into the exponent is the next power of two).  Below 2^-24 the result is
+// 2^-24 with probability |v| / 2^-24, else 0.  Infinities and NaNs convert as they are.
+__device__ __forceinline__ _Float16 f16_sr_any(float v, uint32_t rnd)
 {
-    // FP16 keeps 10 mantissa bits down to 2^-14 (13 FP32 bits below its cut) and a fixed
-    // spacing of 2^-24 below (d = 126 - biased exponent bits below the cut, up to 23);
-    // d random bits (the 16 given, shifted into the top of the d) are added to the
-    // magnitude's pattern and the low d bits cleared, which leaves a multiple of the FP16
-    // spacing (a carry into the exponent is the next power of two).  Below 2^-24 the
-    // result is 2^-24 with probability |v| / 2^-24, else 0.  Infinities and NaNs convert
-    // as they are.
     const uint32_t u = __float_as_uint(v);
     const uint32_t ua = u & 0x7fffffffu;
     const int eb = (int)(ua >> 23);
@@ -251,6 +253,16 @@ __device__ __forceinline__ _Float16 f16_sr(float v, uint32_t rnd)
     if (eb < 103) m = (float)(rnd & 0xffffu) < __uint_as_float(ua) * 0x1p40f ? 0x33800000u : 0u;
     const float q = __uint_as_float(m | (u & 0x80000000u));
     return (_Float16)(eb == 255 ? v : q);
+}
+// The conversion instruction (random bits in the upper half of its operand) rounds every
+// value of FP16's normal range like f16_sr_any (checked on all of them); a wave that holds
+// another value (other than 0) takes the software form.
+__device__ __forceinline__ _Float16 f16_sr(float v, uint32_t rnd)
+{
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    const uint32_t ua = __float_as_uint(v) & 0x7fffffffu;
+    if (__any(ua - 0x38800000u >= 0x477fe000u - 0x38800000u && ua != 0u)) return f16_sr_any(v, rnd);
+    return __builtin_amdgcn_cvt_sr_f16_f32(f16x2{}, v, rnd << 16, false)[0];
 }
 
 __device__ __forceinline__ void rd_st_sr(float *p, int64_t i, float v, uint32_t)
@@ -416,9 +428,10 @@ __device__ __forceinline__ bool on_dirichlet(uint32_t dir, int gx, int gy, int g
 // rounding): `dith` (fp32_dither) is added to the increment before that final addition.
 // rd_update_n takes the active-neighbour count and the wall count as floats (exact small
 // integers), rd_update the neighbour bits; both round identically.
+// self: the species' own index, whose K is 0 (a reaction's product is another species).
 template <int S, bool DTH = false>
 __device__ __forceinline__ float rd_update_n(float uc, const float nbv[6], float nact, float nwall,
-                                             const SpeciesCoef &k, const float *cen, float dith = 0.0f)
+                                             const SpeciesCoef &k, const float *cen, int self, float dith = 0.0f)
 {
     float sum = nbv[0];
 #pragma unroll
@@ -428,15 +441,16 @@ __device__ __forceinline__ float rd_update_n(float uc, const float nbv[6], float
     const float loss = fmaf(k.gamma, nwall, k.beta);
     inc = fmaf(-loss, uc, inc);
 #pragma unroll
-    for (int b = 0; b < S; ++b) inc = fmaf(k.K[b], cen[b], inc);
+    for (int b = 0; b < S; ++b)
+        if (b != self) inc = fmaf(k.K[b], cen[b], inc);
     if constexpr (DTH) inc = inc + dith;
     return uc + inc;
 }
 template <int S, bool DTH = false>
 __device__ __forceinline__ float rd_update(float uc, const float nbv[6], unsigned nbm, int nwall,
-                                           const SpeciesCoef &k, const float *cen, float dith = 0.0f)
+                                           const SpeciesCoef &k, const float *cen, int self, float dith = 0.0f)
 {
-    return rd_update_n<S, DTH>(uc, nbv, (float)__popc(nbm & 63u), (float)nwall, k, cen, dith);
+    return rd_update_n<S, DTH>(uc, nbv, (float)__popc(nbm & 63u), (float)nwall, k, cen, self, dith);
 }
 
 // Stochastic rounding of FP32 values: a dither (u - 1/2) ulp(c), u in [0, 1) from 16

@@ -116,6 +116,7 @@ struct rd_sim {
     double lambda_max() const;
     rd_status check_dt(double dt) const;
     int xcd_chunk(int nb) const;
+    int step_kernel() const;  // the kernel a step launches (`kernel`, by the list's length)
     uint32_t *step_counter() const;
     uint32_t *ticket() const;  // of rd_launch_finish_reduce
     void launch_shape(StepArgs &a) const;
