@@ -656,7 +656,7 @@ rd_status rd_sim::launch_steps(double dt, int64_t n)
         for (int64_t i = 0; i < n; i += fused_steps) {
             const int m = (int)std::min<int64_t>(fused_steps, n - i);
             StepArgs a = step_args(dt, cur);
-            launch_shape(a);
+            a.kernel = kernel;  // the column kernel whatever the list's length
             a.sround = sr ? 1 : 0;
             a.seed = seed;
             a.ctr = step_counter();
