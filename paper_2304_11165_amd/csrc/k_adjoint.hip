@@ -102,12 +102,6 @@ __device__ __forceinline__ uint32_t face_slot8(int f, int u, int v)
     default: return (uint32_t)((0 * 8 + v) * 8 + u);
     }
 }
-// Box faces a voxel lies on (bit d: direction d).
-__device__ __forceinline__ unsigned box_faces8(const GeomInfo &g, int gx, int gy, int gz)
-{
-    return (gx == 0 ? 1u : 0u) | (gx == g.nx - 1 ? 2u : 0u) | (gy == 0 ? 4u : 0u) | (gy == g.ny - 1 ? 8u : 0u) |
-           (gz == 0 ? 16u : 0u) | (gz == g.nz - 1 ? 32u : 0u);
-}
 // Plane z of one field and its four side halos (held by the lanes with ly == z) into a
 // wave's 10 x 10 LDS tile.
 __device__ __forceinline__ void tile_plane(float *t, int lx, int ly, int z, float c, const float side[6])
@@ -213,7 +207,7 @@ __global__ __launch_bounds__(256) void k_adjoint8(AdjArgs a)
         tile_order();
         const float nact = (float)((ncw >> (3 * z)) & 7u);
         unsigned onf = 0u;
-        if (bnd) onf = box_faces8(g, gx, gy, bz * 8 + z);
+        if (bnd) onf = box_faces(g, gx, gy, bz * 8 + z);
         const float nwall = (6.0f - nact) - (float)__popc(onf);
         const int o = (ly + 1) * 10 + (lx + 1);
         const float lp = lc[z];
@@ -481,7 +475,7 @@ __global__ __launch_bounds__(256) void k_adjoint8e(AdjEArgs x)
         settle(gD, gk);
         const float nact = (float)((ncw >> (3 * z)) & 7u);
         unsigned onf = 0u;
-        if (bnd) onf = box_faces8(g, gx, gy, bz * 8 + z);
+        if (bnd) onf = box_faces(g, gx, gy, bz * 8 + z);
         const float nwall = (6.0f - nact) - (float)__popc(onf);
         float out = fmaf(-fmaf(a.coef.gamma, nwall, a.coef.beta), lp, fmaf(a.coef.alpha, laml, lp));
         if (bnd) {

@@ -93,12 +93,6 @@ __device__ __forceinline__ void vox8(const StepArgs &a, const float *ts, int sst
     }
 }
 
-__device__ __forceinline__ unsigned box_faces(const GeomInfo &g, int gx, int gy, int gz)
-{
-    return (gx == 0 ? 1u : 0u) | (gx == g.nx - 1 ? 2u : 0u) | (gy == 0 ? 4u : 0u) |
-           (gy == g.ny - 1 ? 8u : 0u) | (gz == 0 ? 16u : 0u) | (gz == g.nz - 1 ? 32u : 0u);
-}
-
 // Update of one voxel from its precomputed neighbour code (bits 0-5 active neighbours,
 // bit 6 active) and its box-face bits onf (0 for blocks away from the box boundary).
 // Same arithmetic as every other variant (rd_update).

@@ -646,7 +646,23 @@ bool rd_sim::fused_ok() const
     return g->B == 8 && !compact && (kernel == 2 || kernel == 3) && !diff_path();
 }
 
-rd_status rd_sim::launch_steps(double dt, int64_t n)
+// Where two steps go in one launch instead of a column kernel each (same bits; k_pair.hip has
+// the figures of long lists).  A pair is a longer chain per wave, so on short lists it needs
+// cheap updates to gain; us per step, single / pair, packings of 64^3, 80^3, 96^3 (505, 989,
+// 1710 blocks): one species FP32 3.3 / 2.8, 3.7 / 3.0, 4.4 / 3.4, BF16 with stochastic
+// rounding 3.6 / 3.4, 4.1 / 3.5, 4.9 / 4.0, FP16 with it 3.7 / 3.9, 4.2 / 4.0, 5.3 / 4.5;
+// two species FP32 3.8 / 3.6, 4.4 / 4.0, 5.5 / 4.5, with the dither 4.2 / 4.3, 4.9 / 4.8, 6.3
+// / 5.3, FP16 with stochastic rounding 4.2 / 5.0, 4.8 / 5.3, 6.2 / 6.0 and 25.0 / 24.3 at
+// 18 071 blocks: no gain.
+bool rd_sim::pair_ok() const
+{
+    if (g->B != 8 || compact || (kernel != 2 && kernel != 3) || S > 2 || diff_path()) return false;
+    const bool sr16 = sround && storage != RD_FP32;
+    if (g->nb() <= 1024) return S == 1 && !sr16;
+    return S == 1 || !(sr16 && storage == RD_FP16);
+}
+
+rd_status rd_sim::launch_steps(double dt, int64_t n, bool keep)
 {
     // stochastic rounding: at the store for 16-bit storage; for FP32 storage a dither of
     // the increment, in the constant-D kernels only (the kernels with a diffusivity
@@ -667,6 +683,8 @@ rd_status rd_sim::launch_steps(double dt, int64_t n)
         if (sr && n > 0) LAUNCHCHK(rd_launch_add_u32(step_counter(), (uint32_t)n, stream));
         return RD_OK;
     }
+    int64_t paired = pair_ok() ? n & ~(int64_t)1 : 0;  // the steps taken two per launch
+    if (keep && (paired & 2)) paired -= 2;
     for (int64_t i = 0; i < n; ++i) {
         StepArgs a = step_args(dt, cur);
         launch_shape(a);
@@ -674,7 +692,11 @@ rd_status rd_sim::launch_steps(double dt, int64_t n)
         a.seed = seed;
         a.ctr = step_counter();
         a.ctr_off = (uint32_t)i;
-        if (diff_path()) {
+        if (i < paired) {
+            a.xcd_chunk = rd_xcd_order((a.nb + 3) / 4, xcd_map);
+            LAUNCHCHK(rd_launch_step_pair(storage, a, stream));
+            ++i;
+        } else if (diff_path()) {
             // B = 8: the column kernel (with the x-face exchange when kernel 3 is chosen)
             // unless the workgroup-per-block kernel is chosen (then one thread per slot);
             // B = 4: one thread per slot
@@ -730,7 +752,7 @@ rd_status rd_sim::step(double dt, int64_t n)
             stream = cap_stream;
             const int cur0 = cur;
             HIPCHK(hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal));
-            rd_status ls = launch_steps(dt, gs);
+            rd_status ls = launch_steps(dt, gs, true);
             hipGraph_t graph = nullptr;
             hipError_t ce = hipStreamEndCapture(cap_stream, &graph);
             stream = user;

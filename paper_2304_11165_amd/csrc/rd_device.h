@@ -474,6 +474,13 @@ __device__ __forceinline__ int64_t voxel_id(const GeomInfo &g, int gx, int gy, i
     return g.dense0 + ((int64_t)gz * g.ny + gy) * g.nx + gx;
 }
 
+// Bit d set: the voxel lies on box face d (-x, +x, -y, +y, -z, +z).
+__device__ __forceinline__ unsigned box_faces(const GeomInfo &g, int gx, int gy, int gz)
+{
+    return (gx == 0 ? 1u : 0u) | (gx == g.nx - 1 ? 2u : 0u) | (gy == 0 ? 4u : 0u) |
+           (gy == g.ny - 1 ? 8u : 0u) | (gz == 0 ? 16u : 0u) | (gz == g.nz - 1 ? 32u : 0u);
+}
+
 // Block position of list entry b.
 __device__ __forceinline__ void block_pos(const BlockInfo &bi, int *bx, int *by, int *bz, int *gid)
 {

@@ -129,6 +129,9 @@ struct ReduceArgs {
 // ---- launchers (k_step.hip) -------------------------------------------------
 // storage: 0 fp32, 1 bf16, 2 fp16.  All return a hipError_t as int.
 int rd_launch_step(int storage, int B, const StepArgs &a, void *stream);
+// Two steps in one launch (k_pair.hip): B = 8, block layout, one or two species; a.ctr_off
+// is the first step's, the buffers swap once.
+int rd_launch_step_pair(int storage, const StepArgs &a, void *stream);
 // Compact layout, B = 8: the column step with lane-exchanged neighbours (k_compact.hip).
 int rd_launch_step_lanes(int storage, const StepArgs &a, void *stream);
 // rows of partials written by rd_launch_reduce (one per workgroup of four blocks)

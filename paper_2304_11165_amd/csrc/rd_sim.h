@@ -117,10 +117,12 @@ struct rd_sim {
     rd_status check_dt(double dt) const;
     int xcd_chunk(int nb) const;
     int step_kernel() const;  // the kernel a step launches (`kernel`, by the list's length)
+    bool pair_ok() const;      // two steps per launch where possible
     uint32_t *step_counter() const;
     uint32_t *ticket() const;  // of rd_launch_finish_reduce
     void launch_shape(StepArgs &a) const;
-    rd_status launch_steps(double dt, int64_t n);
+    // keep: an even n leaves the buffers in the order they are in now (captured graphs)
+    rd_status launch_steps(double dt, int64_t n, bool keep = false);
     rd_status step(double dt, int64_t n);
     // part < 0: every block; else the blocks of one part of a concatenated geometry
     rd_status balance(int s, double out[RD_NRED], int part = -1);

@@ -1,0 +1,75 @@
+"""Two steps per launch against one step per launch of the persistent kernel, bit for bit:
+boxes that end one voxel into a block, missing neighbour and edge blocks, walls, held faces,
+odd step counts and graphs whose number of launches has to be made even; lists on both
+sides of the length from which every form is paired (1024 blocks)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rd():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2304_11165_amd import rd as rdmod
+
+    return rdmod
+
+
+def _image(shape, fill, blocks):
+    rng = np.random.default_rng(shape[0] * 7 + shape[2])
+    img = rng.random(shape) < fill
+    nb = [-(-n // 8) for n in shape]
+    keep = rng.random(nb) < blocks
+    keep[0, 0, 0] = True
+    for ax in range(3):
+        keep = keep.repeat(8, ax)
+    img &= keep[: shape[0], : shape[1], : shape[2]]
+    img[0, 0, 0] = True
+    return img.astype(np.uint8)
+
+
+def _run(rd, img, species, storage, sround, kernel, steps, gs, graph=True, xcd=False):
+    s = rd.Sim(rd.Geometry(img, None, 1.0, 8), storage)
+    s.add_species(1.0)
+    s.add_reaction(0, -1, 0.0625)
+    s.set_robin(0, 0.125)
+    s.set_dirichlet(0, 0, 1.0)
+    s.set_dirichlet(0, 3, 0.25)
+    s.set_dirichlet(0, 5, 0.75)
+    if species > 1:
+        s.add_species(0.5)
+        s.add_reaction(0, 1, 0.125)
+        s.add_reaction(1, 0, 0.25)
+        s.set_dirichlet(1, 1, 0.5)
+        s.set_dirichlet(1, 4, 1.0)
+    s.set_kernel(kernel, 8)
+    s.set_launch(graph_steps=gs, use_graph=graph, xcd_map=xcd)
+    s.set_rounding(sround, seed=7)
+    s.bind()
+    rng = np.random.default_rng(5)
+    for i in range(species):
+        s.set_field(i, rng.random(img.shape, dtype=np.float32) * img)
+    out = []
+    for n in steps:
+        s.step(0.0625, n)
+        out += [s.get_field(i).cpu().numpy() for i in range(species)]
+    return out
+
+
+@pytest.mark.parametrize("species", [1, 2])
+@pytest.mark.parametrize("storage,sround", [("fp32", 0), ("fp32", 1), ("bf16", 0), ("bf16", 1), ("fp16", 0),
+                                            ("fp16", 1)])
+@pytest.mark.parametrize("shape,fill,blocks", [((8, 8, 8), 0.7, 1.0), ((1, 1, 1), 1.0, 1.0), ((9, 17, 25), 0.9, 1.0),
+                                               ((40, 33, 41), 0.6, 0.6), ((88, 97, 105), 0.6, 0.6),
+                                               ((90, 97, 104), 1.0, 0.9)])
+def test_pairs_agree(rd, species, storage, sround, shape, fill, blocks):
+    img = _image(shape, fill, blocks)
+    steps = (2, 1, 5, 8)
+    want = _run(rd, img, species, storage, sround, "persistent", steps, 8, False)
+    for kernel, gs, graph, xcd in (("column", 8, False, False), ("column_xch", 2, True, False),
+                                   ("column", 6, True, True), ("column", 4, True, False)):
+        got = _run(rd, img, species, storage, sround, kernel, steps, gs, graph, xcd)
+        assert all(np.array_equal(g, w) for g, w in zip(got, want)), (kernel, gs, graph)
