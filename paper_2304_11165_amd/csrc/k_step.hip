@@ -1242,78 +1242,85 @@ __global__ __launch_bounds__(256) void k_gather(const BlockInfo *info, const uin
     }
 }
 
-// The same two copies for 8^3 blocks: one wave per block (lane (lx, ly), eight planes in
-// flight), four consecutive blocks per workgroup and runs of groups per XCD, so that the 32
-// bytes a block holds of a 128-byte line of the dense array meet its x neighbours' in one
-// L2.  One species of the 512^3 soil volume: scatter 151 us, gather 154 us, against 354 and
-// 321 with a workgroup per block.
-template <typename T>
+// The same two copies for 8^3 blocks: a wave holds NZ planes of a block (lane (lx, ly), all in
+// flight).  NZ = 8: four consecutive blocks per workgroup and runs of groups per XCD, so that
+// the 32 bytes a block holds of a 128-byte line of the dense array meet its x neighbours' in
+// one L2.  One species of the 512^3 soil volume: scatter 151 us, gather 154 us, against 354
+// and 321 with a workgroup per block.  NZ = 2: a workgroup per block, for short lists, which
+// do not fill the chip with a wave per block: us with 8 and 2 planes per wave, packings of 505,
+// 1710 and 4063 blocks, scatter 4.8 / 3.1, 5.0 / 4.0, 5.7 / 6.0, gather 3.5 / 2.5, 3.9 / 3.4, 4.8
+// / 5.2.
+template <typename T, int NZ>
 __global__ __launch_bounds__(256) void k_scatter8(const BlockInfo *info, const uint64_t *mask, const uint32_t *cbase,
                                                   const GeomInfo *geom, int nb, int order, const float *dense, T *field,
                                                   uint32_t dir, float d0, float d1, float d2, float d3, float d4,
                                                   float d5)
 {
-    const int lane = threadIdx.x & 63;
-    const int b = __builtin_amdgcn_readfirstlane(map_group(blockIdx.x, order) * 4 + (int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63, grp = map_group(blockIdx.x, order);
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int b = NZ == 8 ? grp * 4 + wv : grp, z0 = NZ == 8 ? 0 : NZ * wv;
     if (b >= nb) return;
     int bx, by, bz, gid;
     block_pos(info[b], &bx, &by, &bz, &gid);
     const GeomInfo g = geom[gid];
     const uint64_t *rec = mask + (int64_t)b * 16;
     const int gx = bx * 8 + (lane & 7), gy = by * 8 + (lane >> 3);
-    const float *col = dense + voxel_id(g, gx, gy, bz * 8);
+    const float *col = dense + voxel_id(g, gx, gy, bz * 8 + z0);
     const int64_t plane = (int64_t)g.nx * g.ny;
-    float v[8];
+    float v[NZ];
 #pragma unroll
-    for (int z = 0; z < 8; ++z) {
+    for (int z = 0; z < NZ; ++z) {
         v[z] = 0.0f;
-        if (lane_bit(rec[z])) v[z] = col[z * plane];
+        if (lane_bit(rec[z0 + z])) v[z] = col[z * plane];
     }
     const float dv[6] = {d0, d1, d2, d3, d4, d5};
-    uint32_t at = cbase ? cbase[b] : 0u;
+    uint32_t at = cbase ? cbase[b] + plane_prefix(rec, z0) : 0u;
 #pragma unroll
-    for (int z = 0; z < 8; ++z) {
-        const uint64_t W = rec[z];
+    for (int z = 0; z < NZ; ++z) {
+        const uint64_t W = rec[z0 + z];
         if (dir && boundary_block(g, bx, by, bz)) {  // uniform; the highest flagged face wins
-            const unsigned onf = box_faces(g, gx, gy, bz * 8 + z) & dir;
+            const unsigned onf = box_faces(g, gx, gy, bz * 8 + z0 + z) & dir;
 #pragma unroll
             for (int f = 0; f < 6; ++f)
                 if (lane_bit(W) && ((onf >> f) & 1u)) v[z] = dv[f];
         }
         // compact layout: only active voxels are stored
-        if (!cbase) rd_st(field, (int64_t)b * 512 + z * 64 + lane, v[z]);
+        if (!cbase) rd_st(field, (int64_t)b * 512 + (z0 + z) * 64 + lane, v[z]);
         else if (lane_bit(W)) rd_st(field, (int64_t)(at + lanes_below(W)), v[z]);
         at += (uint32_t)__popcll(W);
     }
 }
 
-template <typename T>
+template <typename T, int NZ>
 __global__ __launch_bounds__(256) void k_gather8(const BlockInfo *info, const uint64_t *mask, const uint32_t *cbase,
                                                  const GeomInfo *geom, int nb, int order, const T *field, float *dense)
 {
-    const int lane = threadIdx.x & 63;
-    const int b = __builtin_amdgcn_readfirstlane(map_group(blockIdx.x, order) * 4 + (int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63, grp = map_group(blockIdx.x, order);
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int b = NZ == 8 ? grp * 4 + wv : grp, z0 = NZ == 8 ? 0 : NZ * wv;
     if (b >= nb) return;
     int bx, by, bz, gid;
     block_pos(info[b], &bx, &by, &bz, &gid);
     const GeomInfo g = geom[gid];
     const uint64_t *rec = mask + (int64_t)b * 16;
-    float *col = dense + voxel_id(g, bx * 8 + (lane & 7), by * 8 + (lane >> 3), bz * 8);
+    float *col = dense + voxel_id(g, bx * 8 + (lane & 7), by * 8 + (lane >> 3), bz * 8 + z0);
     const int64_t plane = (int64_t)g.nx * g.ny;
-    typename RawOf<T>::type v[8];
-    uint32_t at = cbase ? cbase[b] : 0u;
+    typename RawOf<T>::type v[NZ];
+    uint32_t at = cbase ? cbase[b] + plane_prefix(rec, z0) : 0u;
 #pragma unroll
-    for (int z = 0; z < 8; ++z) {
-        const uint64_t W = rec[z];
+    for (int z = 0; z < NZ; ++z) {
+        const uint64_t W = rec[z0 + z];
         v[z] = (typename RawOf<T>::type)0;
         if (lane_bit(W))
-            v[z] = ld_raw(field, cbase ? (int64_t)(at + lanes_below(W)) : (int64_t)b * 512 + z * 64 + lane);
+            v[z] = ld_raw(field, cbase ? (int64_t)(at + lanes_below(W)) : (int64_t)b * 512 + (z0 + z) * 64 + lane);
         at += (uint32_t)__popcll(W);
     }
 #pragma unroll
-    for (int z = 0; z < 8; ++z)
-        if (lane_bit(rec[z])) col[z * plane] = from_raw<T>(v[z]);
+    for (int z = 0; z < NZ; ++z)
+        if (lane_bit(rec[z0 + z])) col[z * plane] = from_raw<T>(v[z]);
 }
+// planes per wave: 2 up to this many blocks, 8 above
+constexpr int COPY_SHORT = 2048;
 
 // Set the Dirichlet voxels of one species in a block-major field (others untouched).
 template <typename T, int B>
@@ -1535,9 +1542,11 @@ int launch_scatter_t(const BlockInfo *info, const uint64_t *mask, const uint32_t
                      int nb, const float *dense, void *field, uint32_t dir, const float *dv, hipStream_t st)
 {
     if constexpr (B == 8) {
-        const int groups = (nb + 3) / 4, order = rd_xcd_order(groups, false);
-        hipLaunchKernelGGL((k_scatter8<T>), dim3(rd_xcd_grid(groups, order)), dim3(256), 0, st, info, mask, cbase, geom,
-                           nb, order, dense, (T *)field, dir, dv[0], dv[1], dv[2], dv[3], dv[4], dv[5]);
+        const bool few = nb <= COPY_SHORT;
+        const int groups = few ? nb : (nb + 3) / 4, order = rd_xcd_order(groups, false);
+        hipLaunchKernelGGL((few ? k_scatter8<T, 2> : k_scatter8<T, 8>), dim3(rd_xcd_grid(groups, order)), dim3(256), 0,
+                           st, info, mask, cbase, geom, nb, order, dense, (T *)field, dir, dv[0], dv[1], dv[2], dv[3],
+                           dv[4], dv[5]);
     } else
     hipLaunchKernelGGL((k_scatter<T, B>), dim3(nb), dim3(256), 0, st, info, mask, cbase, geom, nb, dense,
                        (T *)field, dir, dv[0], dv[1], dv[2], dv[3], dv[4], dv[5]);
@@ -1548,9 +1557,10 @@ int launch_gather_t(const BlockInfo *info, const uint64_t *mask, const uint32_t 
                     int nb, const void *field, float *dense, hipStream_t st)
 {
     if constexpr (B == 8) {
-        const int groups = (nb + 3) / 4, order = rd_xcd_order(groups, false);
-        hipLaunchKernelGGL((k_gather8<T>), dim3(rd_xcd_grid(groups, order)), dim3(256), 0, st, info, mask, cbase, geom,
-                           nb, order, (const T *)field, dense);
+        const bool few = nb <= COPY_SHORT;
+        const int groups = few ? nb : (nb + 3) / 4, order = rd_xcd_order(groups, false);
+        hipLaunchKernelGGL((few ? k_gather8<T, 2> : k_gather8<T, 8>), dim3(rd_xcd_grid(groups, order)), dim3(256), 0,
+                           st, info, mask, cbase, geom, nb, order, (const T *)field, dense);
     } else
     hipLaunchKernelGGL((k_gather<T, B>), dim3(nb), dim3(256), 0, st, info, mask, cbase, geom, nb,
                        (const T *)field, dense);

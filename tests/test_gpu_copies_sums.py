@@ -1,7 +1,7 @@
-"""Copies between dense fields and block storage (8^3: one wave per block) and the one-launch
-finish of the FP64 sums, around the sizes where their dispatch changes: part blocks at the
-box edges, list lengths around 4096 rows (one workgroup) and above (ranges and a ticket,
-which must be back at 0 for the next sum)."""
+"""Copies between dense fields and block storage (8^3: two planes per wave up to 2048 blocks,
+eight above) and the one-launch finish of the FP64 sums, around the sizes where their dispatch
+changes: part blocks at the box edges, list lengths around 4096 rows (one workgroup) and above
+(ranges and a ticket, which must be back at 0 for the next sum)."""
 import numpy as np
 import pytest
 
@@ -20,7 +20,7 @@ def rd():
 
 @pytest.mark.parametrize("layout", ["blocks", "compact"])
 @pytest.mark.parametrize("storage", ["fp32", "bf16"])
-@pytest.mark.parametrize("shape", [(1, 1, 1), (7, 9, 8), (17, 8, 33), (40, 41, 263)])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (7, 9, 8), (17, 8, 33), (40, 41, 263), (64, 128, 128), (5, 22, 5457)])
 def test_round_trip(rd, shape, storage, layout):
     import torch
 
