@@ -42,7 +42,8 @@ __device__ __forceinline__ float stored(float v, uint32_t rnd)
     else return (float)f16_sr(v, rnd);
 }
 
-template <typename T, int S, bool SR>
+// MID: the first step's field is stored too (a.cmid).
+template <typename T, int S, bool SR, bool MID>
 __device__ __forceinline__ void pair8z(const StepArgs &a)
 {
     constexpr bool DITHER = SR && std::is_same<T, float>::value;
@@ -272,6 +273,16 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
 #pragma unroll
         for (int s = 0; s < S; ++s) u[s][z] = stored<T, SR>(r[s], sr_species(h, s));
     }
+    if constexpr (MID) {  // (rounded already)
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            T *o = uniform_ptr((T *)a.cmid + s * a.sstride + (int64_t)b * 512);
+#pragma unroll
+            for (int z = 0; z < 8; ++z)
+                if (lane_bit(sector_lanes<T>(Wo[z])))
+                    rd_st(at_byte(o, (uint32_t)(z * 64 + lane) * (uint32_t)sizeof(T)), 0, u[s][z]);
+        }
+    }
     wave_sync();
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -302,23 +313,24 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
     }
 }
 
-template <typename T, bool SR>
+template <typename T, bool SR, bool MID>
 __global__ __launch_bounds__(256) void k_pair8z(StepArgs a)
 {
-    pair8z<T, 1, SR>(a);
+    pair8z<T, 1, SR, MID>(a);
 }
 // two species: 32 KB of LDS per workgroup, five waves per SIMD
 template <typename T, bool SR>
 __global__ __launch_bounds__(256, 5) void k_pair8z2(StepArgs a)
 {
-    pair8z<T, 2, SR>(a);
+    pair8z<T, 2, SR, false>(a);
 }
 
 template <typename T>
 void launch_pair_t(const StepArgs &a, int groups, hipStream_t st)
 {
-    if (a.S == 1 && a.sround) hipLaunchKernelGGL((k_pair8z<T, true>), dim3(groups), dim3(256), 0, st, a);
-    else if (a.S == 1) hipLaunchKernelGGL((k_pair8z<T, false>), dim3(groups), dim3(256), 0, st, a);
+    if (a.cmid) hipLaunchKernelGGL((k_pair8z<T, false, true>), dim3(groups), dim3(256), 0, st, a);
+    else if (a.S == 1 && a.sround) hipLaunchKernelGGL((k_pair8z<T, true, false>), dim3(groups), dim3(256), 0, st, a);
+    else if (a.S == 1) hipLaunchKernelGGL((k_pair8z<T, false, false>), dim3(groups), dim3(256), 0, st, a);
     else if (a.sround) hipLaunchKernelGGL((k_pair8z2<T, true>), dim3(groups), dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_pair8z2<T, false>), dim3(groups), dim3(256), 0, st, a);
 }
@@ -327,7 +339,7 @@ void launch_pair_t(const StepArgs &a, int groups, hipStream_t st)
 int rd_launch_step_pair(int storage, const StepArgs &a, void *stream)
 {
     if (a.nb <= 0) return 0;
-    if (a.S < 1 || a.S > 2 || a.cbase) return (int)hipErrorInvalidValue;
+    if (a.S < 1 || a.S > 2 || a.cbase || (a.cmid && (a.S != 1 || a.sround))) return (int)hipErrorInvalidValue;
     const int groups = rd_xcd_grid((a.nb + 3) / 4, a.xcd_chunk);
     if (storage == 0) launch_pair_t<float>(a, groups, (hipStream_t)stream);
     else if (storage == 1) launch_pair_t<bf16_t>(a, groups, (hipStream_t)stream);

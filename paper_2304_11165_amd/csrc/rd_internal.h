@@ -64,6 +64,7 @@ struct StepArgs {
     const GeomInfo *geom;  // indexed by geometry id
     const void *cin;       // T*, species-major
     void *cout;
+    void *cmid;            // rd_launch_step_pair: also receives the first step's field (or NULL)
     int64_t sstride;       // elements between species buffers (nb * B^3)
     int32_t nb;            // blocks in the list
     int32_t S;             // species
@@ -130,7 +131,7 @@ struct ReduceArgs {
 // storage: 0 fp32, 1 bf16, 2 fp16.  All return a hipError_t as int.
 int rd_launch_step(int storage, int B, const StepArgs &a, void *stream);
 // Two steps in one launch (k_pair.hip): B = 8, block layout, one or two species; a.ctr_off
-// is the first step's, the buffers swap once.
+// is the first step's, the buffers swap once.  a.cmid: one species, rounding to nearest.
 int rd_launch_step_pair(int storage, const StepArgs &a, void *stream);
 // Compact layout, B = 8: the column step with lane-exchanged neighbours (k_compact.hip).
 int rd_launch_step_lanes(int storage, const StepArgs &a, void *stream);

@@ -697,10 +697,10 @@ extern "C" void rd_batch_destroy(rd_batch *b) { delete b; }
 // adjoint
 // ---------------------------------------------------------------------------
 
-// Checkpointed adjoint: a forward sweep stores c^{jk} every k steps; the backward
-// sweep restores each segment's first state, recomputes the segment's states into
-// k-1 spare slots with the same step kernel (bitwise the forward states) and runs
-// the adjoint steps from the segment's end to its start.
+// Checkpointed adjoint: a forward sweep stores c^{jk} every k steps and, in the last
+// segment, every state; the backward sweep recomputes each earlier segment's states from its
+// first into the same k-1 spare slots (bitwise the forward states) and runs the adjoint
+// steps from the segment's end to its start.
 static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode, int64_t n_steps, double dt,
                               int checkpoint_every, double *loss, double *dL_dD, double *dL_drate,
                               double *dev_dL_de)
@@ -755,10 +755,47 @@ static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode,
     LAUNCHCHK(rd_launch_scatter(0, B, (const BlockInfo *)(ws + sim->L.info),
                                 (const uint64_t *)(ws + sim->L.mask), nullptr, (const GeomInfo *)(ws + sim->L.geom),
                                 nb, dev_seed, seed, 0u, zero6, stream));
-    // forward with checkpoints
+    // len steps from state(0), each one's field into state(m): two per launch where the
+    // simulation's own steps are paired (both fields stored), else one
+    const StepArgs fa = sim->step_args(dt, sim->cur);
+    auto run_states = [&](int64_t len, auto state) -> rd_status {
+        for (int64_t m = 1; m <= len; ++m) {
+            StepArgs sa = fa;
+            sa.cin = state(m - 1);
+            sa.cout = state(m);
+            sa.sround = 0;
+            sa.ctr = sim->step_counter();
+            sa.ctr_off = 0;
+            sim->launch_shape(sa);
+            if (fac) {  // the inhomogeneous step, as rd_sim_step runs it
+                const int column = B == 8 && sim->kernel != 0 ? 1 : 0;
+                sa.xcd_chunk = column ? rd_xcd_order((nb + 3) / 4, sim->xcd_map) : 0;
+                DiffArgs da{sa, efac, {0.0f, 0.0f, 0.0f, 0.0f}};
+                LAUNCHCHK(rd_launch_step_diff(st, B, da, column, stream));
+            } else if (m < len && sim->pair_ok()) {
+                sa.cmid = state(m);
+                sa.cout = state(++m);
+                sa.xcd_chunk = rd_xcd_order((nb + 3) / 4, sim->xcd_map);
+                LAUNCHCHK(rd_launch_step_pair(st, sa, stream));
+            } else {
+                LAUNCHCHK(rd_launch_step(st, B, sa, stream));
+            }
+        }
+        return RD_OK;
+    };
+    // forward with checkpoints; the last segment keeps every state where the backward sweep,
+    // which starts with it, would recompute them (19 steps of the 95 recomputed at 5
+    // segments of 20)
     for (int64_t j = 0; j < ncp; ++j) {
-        HIPCHK(hipMemcpyAsync(slot(j), sim->field_ptr(sim->cur, 0), fbytes, hipMemcpyDeviceToDevice, stream));
-        s = sim->step(dt, std::min<int64_t>(k, n_steps - j * k));
+        const int64_t len = std::min<int64_t>(k, n_steps - j * k);
+        void *field = sim->field_ptr(sim->cur, 0);
+        HIPCHK(hipMemcpyAsync(slot(j), field, fbytes, hipMemcpyDeviceToDevice, stream));
+        if (j < ncp - 1) {
+            s = sim->step(dt, len);
+        } else {
+            s = run_states(len, [&](int64_t m) { return m == 0 ? slot(j) : m < len ? slot(ncp + m - 1) : field; });
+            sim->steps_taken += len;
+        }
         if (s != RD_OK) return s;
     }
     AdjArgs a{};
@@ -769,7 +806,6 @@ static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode,
     a.ncnt = B == 8 ? (const uint32_t *)(ws + sim->L.ncnt) : nullptr;
     a.nb = nb;
     a.order = rd_xcd_order((nb + 3) / 4, false);
-    const StepArgs fa = sim->step_args(dt, sim->cur);
     a.coef = fa.coef[0];
     a.seed = seed;
     a.partial = (double *)(ws + sim->L.part);
@@ -791,23 +827,7 @@ static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode,
         const int64_t len = std::min<int64_t>(k, n_steps - s0);
         // seg[0] = checkpoint j, seg[m] = spare slot ncp + m - 1
         auto seg = [&](int64_t m) { return m == 0 ? slot(j) : slot(ncp + m - 1); };
-        for (int64_t m = 1; m < len; ++m) {
-            StepArgs sa = fa;
-            sa.cin = seg(m - 1);
-            sa.cout = seg(m);
-            sa.sround = 0;
-            sa.ctr = sim->step_counter();
-            sa.ctr_off = 0;
-            sim->launch_shape(sa);
-            if (fac) {  // the inhomogeneous step, as rd_sim_step runs it
-                const int column = B == 8 && sim->kernel != 0 ? 1 : 0;
-                sa.xcd_chunk = column ? rd_xcd_order((nb + 3) / 4, sim->xcd_map) : 0;
-                DiffArgs da{sa, efac, {0.0f, 0.0f, 0.0f, 0.0f}};
-                LAUNCHCHK(rd_launch_step_diff(st, B, da, column, stream));
-            } else {
-                LAUNCHCHK(rd_launch_step(st, B, sa, stream));
-            }
-        }
+        if (j < ncp - 1 && (s = run_states(len - 1, seg)) != RD_OK) return s;
         for (int64_t m = len - 1; m >= 0; --m) {
             a.c = seg(m);
             a.lam_in = lam[lc];

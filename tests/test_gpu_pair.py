@@ -73,3 +73,33 @@ def test_pairs_agree(rd, species, storage, sround, shape, fill, blocks):
                                    ("column", 6, True, True), ("column", 4, True, False)):
         got = _run(rd, img, species, storage, sround, kernel, steps, gs, graph, xcd)
         assert all(np.array_equal(g, w) for g, w in zip(got, want)), (kernel, gs, graph)
+
+
+# The adjoint keeps the last segment's states and recomputes the others', two steps per launch
+# with the column kernels: any segment length (odd and even, one segment, single steps) gives
+# the same states, hence the same sums, as single steps of the workgroup kernel.
+@pytest.mark.parametrize("storage", ["fp32", "fp16"])
+@pytest.mark.parametrize("shape", [(9, 17, 25), (88, 97, 105)])
+def test_adjoint_states(rd, storage, shape):
+    img = _image(shape, 0.7, 0.9)
+    rng = np.random.default_rng(2)
+    c0 = rng.random(shape, dtype=np.float32) * img
+    target = rng.random(shape, dtype=np.float32) * img
+
+    def run(kernel, every):
+        import torch
+
+        s = rd.Sim(rd.Geometry(img, None, 1.0, 8), storage)
+        s.add_species(1.0)
+        s.add_reaction(0, -1, 0.0625)
+        s.set_dirichlet(0, 0, 1.0)
+        s.set_kernel(kernel, 8)
+        s.bind(features=rd.RD_WS_ADJOINT, checkpoint_slots=-(-9 // every) + every - 1)
+        s.set_field(0, c0)
+        got = s.adjoint(torch.as_tensor(target, device="cuda"), 9, 0.0625, every)
+        return [float(v) for v in got], s.get_field(0).cpu().numpy()
+
+    want = run("block", 4)
+    for every in (1, 2, 3, 4, 9):
+        got = run("column", every)
+        assert got[0] == want[0] and np.array_equal(got[1], want[1]), every
