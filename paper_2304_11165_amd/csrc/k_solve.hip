@@ -720,9 +720,10 @@ __global__ __launch_bounds__(256) void k_cg_segsum(const double *part, const Geo
 // for the next launch) sums those and runs cg_scalars.  Nothing waits for another
 // workgroup, and the order of every addition is fixed: thread t of a range adds rows t, t
 // + 256, ..., then a tree (threads 128, 64, ... apart), as k_finish_rows adds them.  On a
-// 208^3 foam (17 000 rows) it takes 8.0 us where three launches (ranges, range sums,
-// scalars) took 15.0, twice per iteration beside 46 + 32 us of the CG kernels; one workgroup
-// of 1024 threads took 14.6 (one CU's bandwidth), so the ranges stay spread over the chip.
+// 208^3 foam (17 000 rows) it takes 5.9 us (8.0 with a release of the ticket, which writes back
+// the L2) where three launches (ranges, range sums, scalars) took 15.0, twice per iteration
+// beside 39 + 26 us of the CG kernels; one workgroup of 1024 threads took 14.6 (one CU's
+// bandwidth), so the ranges stay spread over the chip.
 constexpr int CG_RANGES = 256;
 __device__ __forceinline__ double range_tree(const double *sh, int lane)  // 256 values, in wave 0
 {
@@ -757,19 +758,16 @@ __global__ __launch_bounds__(256) void k_cg_segsum_long(const double2 *part, int
     s0 = range_tree(sh[0], t);
     s1 = range_tree(sh[1], t);
     uint32_t arrived = 0u;
-    if (t == 0) {
-        __hip_atomic_store(mid + 2 * g, s0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(mid + 2 * g + 1, s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        arrived = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (t < 2) put_agent(mid + 2 * g + t, t == 0 ? s0 : s1);
+    if (t == 0) arrived = arrive_agent(count);
     if (__builtin_amdgcn_readfirstlane(arrived) != gridDim.x - 1) return;
     double m0[4], m1[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int j = t + 64 * k;
         const bool in = j < (int)gridDim.x;
-        m0[k] = in ? __hip_atomic_load(mid + 2 * j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
-        m1[k] = in ? __hip_atomic_load(mid + 2 * j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+        m0[k] = in ? get_agent(mid + 2 * j) : 0.0;
+        m1[k] = in ? get_agent(mid + 2 * j + 1) : 0.0;
     }
     s0 = wave_sum((m0[0] + m0[2]) + (m0[1] + m0[3]));
     s1 = wave_sum((m1[0] + m1[2]) + (m1[1] + m1[3]));

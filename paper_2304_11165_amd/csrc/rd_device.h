@@ -597,6 +597,24 @@ struct BlockMasks {
     }
 };
 
+// ---- values handed to another workgroup of the same launch ------------------------
+// v at p, performed where every XCD sees it when this returns (an exchange, whose old value
+// is waited for); get_agent reads it there.  A count raised afterwards (arrive_agent, relaxed)
+// then needs no release fence, which would write back the dirty lines of the XCD's L2.
+__device__ __forceinline__ void put_agent(double *p, double v)
+{
+    const double old = __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::"v"(old) : "memory");
+}
+__device__ __forceinline__ double get_agent(const double *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t arrive_agent(uint32_t *count)
+{
+    return __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Wave-level FP64 sum in a fixed butterfly order (deterministic): partners 32, 16, 8, 4, 2
 // and 1 lanes away.  All 64 lanes must be active.  The half and row swaps and the row
 // rotations stay in the vector unit (after the step of distance 2 d every value repeats
