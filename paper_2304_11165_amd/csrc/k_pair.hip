@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "rd_device.h"
+#include "rd_diff.h"
 
 namespace {
 constexpr int PY = 10, PZ = 100;  // strides of the 10^3 tile of a wave
@@ -42,12 +43,14 @@ __device__ __forceinline__ float stored(float v, uint32_t rnd)
     else return (float)f16_sr(v, rnd);
 }
 
-// MID: the first step's field is stored too (a.cmid).
-template <typename T, int S, bool SR, bool MID>
-__device__ __forceinline__ void pair8z(const StepArgs &a)
+// MID: the first step's field is stored too (a.cmid).  FAC: with the diffusivity factor fe,
+// the operations of k_step8e (FP32 rounds to nearest); its halo is the fields', and the face
+// voxels' code bytes tell which of their neighbours are active.
+template <typename T, int S, bool SR, bool MID, bool FAC>
+__device__ __forceinline__ void pair8z(const StepArgs &a, const float *fe)
 {
-    constexpr bool DITHER = SR && std::is_same<T, float>::value;
-    __shared__ float tile[4][S][1000];
+    constexpr bool DITHER = !FAC && SR && std::is_same<T, float>::value;
+    __shared__ float tile[4][FAC ? S + 1 : S][1000];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int b = __builtin_amdgcn_readfirstlane(map_group(blockIdx.x, a.xcd_chunk) * 4 + wv);
     if (b >= a.nb) return;
@@ -69,13 +72,17 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
     for (int f = 0; f < 6; ++f) Wf[f] = rec[8 + f];
     typedef typename RawOf<T>::type R;
     R rc[S][8], r1[S][6], r2[S][6], re[S][2];
+    float ec[8], e1[6], e2[6], ee[2];  // FAC: the factor
+    const float *eown = FAC ? uniform_ptr(fe + (int64_t)b * 512) : nullptr;
     const uint32_t ncw = a.ncnt[(int64_t)b * 64 + lane];
     uint32_t fcw[6];
 #pragma unroll
     for (int z = 0; z < 8; ++z) {
 #pragma unroll
         for (int s = 0; s < S; ++s) rc[s][z] = (R)0;
+        ec[z] = 0.0f;
         if (lane_bit(Wo[z])) {
+            if (FAC) ec[z] = *at_byte(eown, (uint32_t)(z * 64 + lane) * 4u);
 #pragma unroll
             for (int s = 0; s < S; ++s)
                 rc[s][z] = ld_raw(at_byte(own[s], (uint32_t)(z * 64 + lane) * (uint32_t)sizeof(T)), 0);
@@ -99,8 +106,15 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
         for (int s = 0; s < S; ++s) r1[s][f] = r2[s][f] = (R)0;
         // (the count word unconditionally: under the predicate its extraction would be folded
         // into the branch and wait there for the loads before it)
-        fcw[f] = *at_byte(uniform_ptr(a.ncnt + (int64_t)n * 64), (uint32_t)col * 4u);
+        if (FAC) fcw[f] = *at_byte(uniform_ptr(a.code + (int64_t)n * 512), (uint32_t)s1);
+        else fcw[f] = *at_byte(uniform_ptr(a.ncnt + (int64_t)n * 64), (uint32_t)col * 4u);
+        e1[f] = e2[f] = 0.0f;
         if (lane_bit(Wf[f])) {
+            if (FAC) {
+                const float *nb = uniform_ptr(fe + (int64_t)n * 512);
+                e1[f] = *at_byte(nb, (uint32_t)s1 * 4u);
+                e2[f] = *at_byte(nb, (uint32_t)s2 * 4u);
+            }
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 const T *nb = uniform_ptr(cin + s * a.sstride + (int64_t)n * 512);
@@ -138,10 +152,13 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
     const int es1 = (sb ? 0 : 448) + (sa ? 0 : 56) + lx;
     // without a predicate, the block's first slot where the edge block is missing (a select at
     // the use: a predicated value was copied, and waited for, between the two loads)
+    const int64_t eo[2] = {eb[0] >= 0 ? (int64_t)eb[0] * 512 + es0 : (int64_t)b * 512,
+                           eb[1] >= 0 ? (int64_t)eb[1] * 512 + es1 : (int64_t)b * 512};
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        re[s][0] = ld_raw(cin + s * a.sstride, eb[0] >= 0 ? (int64_t)eb[0] * 512 + es0 : (int64_t)b * 512);
-        re[s][1] = ld_raw(cin + s * a.sstride, eb[1] >= 0 ? (int64_t)eb[1] * 512 + es1 : (int64_t)b * 512);
+    for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) re[s][k] = ld_raw(cin + s * a.sstride, eo[k]);
+        ee[k] = FAC ? fe[eo[k]] : 0.0f;
     }
 
     // all loads are issued
@@ -165,6 +182,15 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
         }
         t[ep0] = eb[0] >= 0 ? from_raw<T>(re[s][0]) : 0.0f;
         if (lane < 32) t[tpos(lx, sa ? 8 : -1, sb ? 8 : -1)] = eb[1] >= 0 ? from_raw<T>(re[s][1]) : 0.0f;
+    }
+    if constexpr (FAC) {
+        float *t = tile[wv][S];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) t[tpos(lx, ly, z)] = ec[z];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) t[fp[f]] = e1[f];
+        t[ep0] = eb[0] >= 0 ? ee[0] : 0.0f;
+        if (lane < 32) t[tpos(lx, sa ? 8 : -1, sb ? 8 : -1)] = eb[1] >= 0 ? ee[1] : 0.0f;
     }
     wave_sync();
 
@@ -191,7 +217,7 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
     }
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
-        fna[f] = (float)((fcw[f] >> (f == 4 ? 21 : f == 5 ? 0 : 3 * ly)) & 7u);
+        fna[f] = FAC ? (float)__popc(fcw[f] & 63u) : (float)((fcw[f] >> (f == 4 ? 21 : f == 5 ? 0 : 3 * ly)) & 7u);
         fnw[f] = 6.0f - fna[f];
 #pragma unroll
         for (int s = 0; s < S; ++s) Uf[s][f] = Wf[f];
@@ -219,7 +245,20 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
             for (int s = 0; s < S; ++s) Uf[s][f] &= ~__ballot((onf & a.coef[s].dir) != 0u);
         }
     }
-    auto update = [&](int s, const float *cen, const float *nbv, float nact, float nwall, uint64_t U, uint32_t h) {
+    auto update = [&](int s, const float *cen, const float *nbv, const float *w, float nact, float nwall, uint64_t U,
+                      uint32_t h) {
+        if constexpr (FAC) {  // as k_step8e
+            const SpeciesCoef &k = a.coef[s];
+            const float uc = cen[s];
+            float lap = 0.0f;
+#pragma unroll
+            for (int d = 0; d < 6; ++d) lap = fmaf(w[d], nbv[d] - uc, lap);
+            float r = fmaf(k.alpha, lap, uc);
+            r = fmaf(-fmaf(k.gamma, nwall, k.beta), uc, r);
+#pragma unroll
+            for (int q = 0; q < S; ++q) r = fmaf(k.K[q], cen[q], r);
+            return lane_bit(U) ? r : uc;
+        }
         const float dth = DITHER ? fp32_dither(cen[s], sr_species(h, s)) : 0.0f;
         const float r = rd_update_n<S, DITHER>(cen[s], nbv, nact, nwall, a.coef[s], cen, s, dth);
         return lane_bit(U) ? r : cen[s];
@@ -238,30 +277,50 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
             float cen[S];
 #pragma unroll
             for (int s = 0; s < S; ++s) cen[s] = h1[s][f];
+            float w[6];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                w[q] = 0.0f;
+                if (FAC) {
+                    const float en_ = q == f ? e2[f] : tile[wv][FAC ? S : 0][fp[f] + (q == f ? 0 : off[q])];
+                    w[q] = (fcw[f] >> q) & 1u ? 0.5f * (e1[f] + en_) : 0.0f;
+                }
+            }
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 const float *p = tile[wv][s] + fp[f];
                 float nbv[6];
 #pragma unroll
                 for (int d = 0; d < 6; ++d) nbv[d] = d == f ? h2[s][f] : p[d == f ? 0 : off[d]];
-                r[s] = stored<T, SR>(update(s, cen, nbv, fna[f], fnw[f], Uf[s][f], h), sr_species(h, s));
+                r[s] = stored<T, SR>(update(s, cen, nbv, w, fna[f], fnw[f], Uf[s][f], h), sr_species(h, s));
             }
         }
 #pragma unroll
         for (int s = 0; s < S; ++s) h2[s][f] = r[s];
     }
+    BlockMasks M;  // FAC: which faces of the block's voxels join two active ones
+    if constexpr (FAC) M.load(rec);
+    auto weight = [](float ep, float eq, uint64_t both) { return lane_bit(both) ? 0.5f * (ep + eq) : 0.0f; };
     // one step of plane z, from the values v of the block's column, the layers below and above
     // and the tile
     auto plane = [&](int z, const float (*v)[8], const float (*hz)[6], uint32_t h, float *r) {
         float cen[S];
 #pragma unroll
         for (int s = 0; s < S; ++s) cen[s] = v[s][z];
+        float w[6];
+        if constexpr (FAC) {
+            const float *p = tile[wv][S] + tpos(lx, ly, z);
+            const float en_[6] = {p[-1], p[1], p[-PY], p[PY], z == 0 ? e1[4] : ec[z > 0 ? z - 1 : 0],
+                                  z == 7 ? e1[5] : ec[z < 7 ? z + 1 : 7]};
+#pragma unroll
+            for (int q = 0; q < 6; ++q) w[q] = weight(ec[z], en_[q], M.pair(z, q));
+        }
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const float *p = tile[wv][s] + tpos(lx, ly, z);
             const float nbv[6] = {p[-1], p[1], p[-PY], p[PY], z == 0 ? hz[s][4] : v[s][z > 0 ? z - 1 : 0],
                                   z == 7 ? hz[s][5] : v[s][z < 7 ? z + 1 : 7]};
-            r[s] = update(s, cen, nbv, na[z], nw[z], Uo[s][z], h);
+            r[s] = update(s, cen, nbv, w, na[z], nw[z], Uo[s][z], h);
         }
     };
     float u[S][8];
@@ -316,13 +375,21 @@ __device__ __forceinline__ void pair8z(const StepArgs &a)
 template <typename T, bool SR, bool MID>
 __global__ __launch_bounds__(256) void k_pair8z(StepArgs a)
 {
-    pair8z<T, 1, SR, MID>(a);
+    pair8z<T, 1, SR, MID, false>(a, nullptr);
 }
 // two species: 32 KB of LDS per workgroup, five waves per SIMD
 template <typename T, bool SR>
 __global__ __launch_bounds__(256, 5) void k_pair8z2(StepArgs a)
 {
-    pair8z<T, 2, SR, false>(a);
+    pair8z<T, 2, SR, false, false>(a, nullptr);
+}
+// One species with the factor: 32 KB of LDS per workgroup.  us per step, k_step8e without and
+// with the x-face exchange / a pair: FP32 packing 64^3 5.1, 6.2 / 4.1, 160^3 14.8, 16.2 / 12.3,
+// soil 256^3 25.1, 28.1 / 21.9; BF16 with stochastic rounding 160^3 14.4, 14.8 / 13.3.
+template <typename T, bool SR, bool MID>
+__global__ __launch_bounds__(256, 5) void k_pair8e(StepArgs a, const float *e)
+{
+    pair8z<T, 1, SR, MID, true>(a, e);
 }
 
 template <typename T>
@@ -334,7 +401,29 @@ void launch_pair_t(const StepArgs &a, int groups, hipStream_t st)
     else if (a.sround) hipLaunchKernelGGL((k_pair8z2<T, true>), dim3(groups), dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_pair8z2<T, false>), dim3(groups), dim3(256), 0, st, a);
 }
+template <typename T>
+void launch_pair_e(const StepArgs &a, const float *e, int groups, hipStream_t st)
+{
+    // FP32 rounds to nearest with the factor
+    const bool sr = a.sround && !std::is_same<T, float>::value;
+    if (a.cmid) hipLaunchKernelGGL((k_pair8e<T, false, true>), dim3(groups), dim3(256), 0, st, a, e);
+    else if (sr)
+        hipLaunchKernelGGL((k_pair8e<T, !std::is_same<T, float>::value, false>), dim3(groups), dim3(256), 0, st, a, e);
+    else hipLaunchKernelGGL((k_pair8e<T, false, false>), dim3(groups), dim3(256), 0, st, a, e);
+}
 }  // namespace
+
+int rd_launch_step_pair_diff(int storage, const DiffArgs &d, void *stream)
+{
+    const StepArgs &a = d.s;
+    if (a.nb <= 0) return 0;
+    if (a.S != 1 || a.cbase || (a.cmid && a.sround)) return (int)hipErrorInvalidValue;
+    const int groups = rd_xcd_grid((a.nb + 3) / 4, a.xcd_chunk);
+    if (storage == 0) launch_pair_e<float>(a, d.e, groups, (hipStream_t)stream);
+    else if (storage == 1) launch_pair_e<bf16_t>(a, d.e, groups, (hipStream_t)stream);
+    else launch_pair_e<_Float16>(a, d.e, groups, (hipStream_t)stream);
+    return (int)hipGetLastError();
+}
 
 int rd_launch_step_pair(int storage, const StepArgs &a, void *stream)
 {

@@ -24,6 +24,9 @@ struct DiffArgs {
 // z-columns; column = 2: the same with the x faces of x-adjacent blocks of a workgroup
 // handed over through LDS; column = 0: one thread per slot.  All give the same bits.
 int rd_launch_step_diff(int storage, int B, const DiffArgs &a, int column, void *stream);
+// Two steps in one launch (k_pair.hip): B = 8, block layout, one species, no sink; as
+// rd_launch_step_pair.
+int rd_launch_step_pair_diff(int storage, const DiffArgs &a, void *stream);
 
 // Fill e from a dense float32 (nz, ny, nx) device array: mode 0 copies the values,
 // mode 1 maps a signed distance phi to d_min + d_max / (1 + exp(-(g1 + g2 phi))),

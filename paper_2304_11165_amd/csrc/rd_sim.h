@@ -118,6 +118,7 @@ struct rd_sim {
     int xcd_chunk(int nb) const;
     int step_kernel() const;  // the kernel a step launches (`kernel`, by the list's length)
     bool pair_ok() const;      // two steps per launch where possible
+    bool pair_diff_ok() const; // the same with the diffusivity factor
     uint32_t *step_counter() const;
     uint32_t *ticket() const;  // of rd_launch_finish_reduce
     void launch_shape(StepArgs &a) const;

@@ -767,16 +767,17 @@ static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode,
             sa.ctr = sim->step_counter();
             sa.ctr_off = 0;
             sim->launch_shape(sa);
-            if (fac) {  // the inhomogeneous step, as rd_sim_step runs it
+            if (m < len && (fac ? sim->pair_diff_ok() : sim->pair_ok())) {
+                sa.cmid = state(m);
+                sa.cout = state(++m);
+                sa.xcd_chunk = rd_xcd_order((nb + 3) / 4, sim->xcd_map);
+                if (fac) LAUNCHCHK(rd_launch_step_pair_diff(st, DiffArgs{sa, efac, {}}, stream));
+                else LAUNCHCHK(rd_launch_step_pair(st, sa, stream));
+            } else if (fac) {  // the inhomogeneous step, as rd_sim_step runs it
                 const int column = B == 8 && sim->kernel != 0 ? 1 : 0;
                 sa.xcd_chunk = column ? rd_xcd_order((nb + 3) / 4, sim->xcd_map) : 0;
                 DiffArgs da{sa, efac, {0.0f, 0.0f, 0.0f, 0.0f}};
                 LAUNCHCHK(rd_launch_step_diff(st, B, da, column, stream));
-            } else if (m < len && sim->pair_ok()) {
-                sa.cmid = state(m);
-                sa.cout = state(++m);
-                sa.xcd_chunk = rd_xcd_order((nb + 3) / 4, sim->xcd_map);
-                LAUNCHCHK(rd_launch_step_pair(st, sa, stream));
             } else {
                 LAUNCHCHK(rd_launch_step(st, B, sa, stream));
             }

@@ -103,3 +103,68 @@ def test_adjoint_states(rd, storage, shape):
     for every in (1, 2, 3, 4, 9):
         got = run("column", every)
         assert got[0] == want[0] and np.array_equal(got[1], want[1]), every
+
+
+# The same with a diffusivity factor (zeros among its values), against the kernel with one
+# thread per slot, and the gradient with respect to the factor.
+@pytest.mark.parametrize("storage,sround", [("fp32", 0), ("fp32", 1), ("bf16", 0), ("bf16", 1), ("fp16", 1)])
+@pytest.mark.parametrize("shape,fill,blocks", [((8, 8, 8), 0.7, 1.0), ((1, 1, 1), 1.0, 1.0), ((9, 17, 25), 0.9, 1.0),
+                                               ((40, 33, 41), 0.6, 0.6), ((90, 97, 104), 1.0, 0.9)])
+def test_factor_pairs(rd, storage, sround, shape, fill, blocks):
+    img = _image(shape, fill, blocks)
+    rng = np.random.default_rng(8)
+    e = rng.random(shape, dtype=np.float32)
+    e[rng.random(shape) < 0.1] = 0.0
+    c0 = rng.random(shape, dtype=np.float32) * img
+
+    def run(kernel, steps, gs):
+        s = rd.Sim(rd.Geometry(img, None, 1.0, 8), storage)
+        s.add_species(1.0)
+        s.add_reaction(0, -1, 0.0625)
+        s.set_robin(0, 0.125)
+        s.set_dirichlet(0, 0, 1.0)
+        s.set_dirichlet(0, 3, 0.25)
+        s.set_dirichlet(0, 5, 0.75)
+        s.set_kernel(kernel, 8)
+        s.set_launch(graph_steps=gs, use_graph=True, xcd_map=False)
+        s.set_rounding(sround, seed=7)
+        s.bind(features=rd.RD_WS_DIFFUSIVITY)
+        s.set_diffusivity(e)
+        s.set_field(0, c0)
+        out = []
+        for n in steps:
+            s.step(0.0625, n)
+            out.append(s.get_field(0).cpu().numpy())
+        return out
+
+    want = run("block", (2, 1, 5, 8), 8)
+    for kernel, gs in (("column", 4), ("column_xch", 6)):
+        got = run(kernel, (2, 1, 5, 8), gs)
+        assert all(np.array_equal(g, w) for g, w in zip(got, want)), kernel
+
+
+@pytest.mark.parametrize("shape", [(9, 17, 25), (40, 33, 41)])
+def test_adjoint_factor_states(rd, shape):
+    import torch
+
+    img = _image(shape, 0.7, 0.9)
+    rng = np.random.default_rng(2)
+    c0, target = (rng.random(shape, dtype=np.float32) * img for _ in range(2))
+    e = rng.random(shape, dtype=np.float32)
+
+    def run(every):
+        s = rd.Sim(rd.Geometry(img, None, 1.0, 8), "fp32")
+        s.add_species(1.0)
+        s.add_reaction(0, -1, 0.0625)
+        s.set_dirichlet(0, 0, 1.0)
+        s.set_kernel("column", 8)
+        s.bind(features=rd.RD_WS_ADJOINT | rd.RD_WS_DIFFUSIVITY, checkpoint_slots=-(-9 // every) + every - 1)
+        s.set_diffusivity(e)
+        s.set_field(0, c0)
+        loss, gD, gk, ge = s.adjoint_factor(torch.as_tensor(target, device="cuda"), 9, 0.0625, every)
+        return (loss, gD, gk), ge.cpu().numpy(), s.get_field(0).cpu().numpy()
+
+    want = run(1)  # single steps only
+    for every in (2, 4, 9):
+        got = run(every)
+        assert got[0] == want[0] and np.array_equal(got[1], want[1]) and np.array_equal(got[2], want[2]), every
