@@ -221,7 +221,9 @@ rd_status rd_sim_set_layout(rd_sim *sim, int layout);
  *               as 0 by range checking, no predicates) and the +-x / +-y neighbours
  *               exchanged between lanes (DPP row shifts, ds_bpermute) instead of an
  *               LDS tile.
- * Results are bitwise identical.  RD_ERR_ARG for kernel outside 0..4 or wg_per_cu
+ * Results are bitwise identical.  Kernels 2 and 3 take two steps per launch where that is
+ * faster (block layout, one or two species) and leave short block lists to kernel 0.
+ * RD_ERR_ARG for kernel outside 0..4 or wg_per_cu
  * outside 1..32; RD_ERR_STATE for kernel 0 or 1 with the compact layout and for
  * kernel 4 with the block layout. */
 rd_status rd_sim_set_kernel(rd_sim *sim, int kernel, int wg_per_cu);

@@ -669,7 +669,7 @@ bool rd_sim::pair_diff_ok() const
     return g->B == 8 && !compact && (kernel == 2 || kernel == 3) && S == 1 && diff_on && !sink_active();
 }
 
-rd_status rd_sim::launch_steps(double dt, int64_t n, bool keep)
+rd_status rd_sim::launch_steps(double dt, int64_t n)
 {
     // stochastic rounding: at the store for 16-bit storage; for FP32 storage a dither of
     // the increment, in the constant-D kernels only (the kernels with a diffusivity
@@ -691,7 +691,16 @@ rd_status rd_sim::launch_steps(double dt, int64_t n, bool keep)
         return RD_OK;
     }
     int64_t paired = pair_ok() || pair_diff_ok() ? n & ~(int64_t)1 : 0;  // the steps taken two per launch
-    if (keep && (paired & 2)) paired -= 2;
+    if (paired & 2) {
+        // under capture (the library's own or a caller's) the number of launches stays even
+        // for an even n: a replay must find the buffers in the order they were captured in
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+            (void)hipGetLastError();
+            cs = hipStreamCaptureStatusActive;
+        }
+        if (cs != hipStreamCaptureStatusNone) paired -= 2;
+    }
     for (int64_t i = 0; i < n; ++i) {
         StepArgs a = step_args(dt, cur);
         launch_shape(a);
@@ -761,7 +770,7 @@ rd_status rd_sim::step(double dt, int64_t n)
             stream = cap_stream;
             const int cur0 = cur;
             HIPCHK(hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal));
-            rd_status ls = launch_steps(dt, gs, true);
+            rd_status ls = launch_steps(dt, gs);
             hipGraph_t graph = nullptr;
             hipError_t ce = hipStreamEndCapture(cap_stream, &graph);
             stream = user;

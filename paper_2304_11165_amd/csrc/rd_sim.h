@@ -122,8 +122,7 @@ struct rd_sim {
     uint32_t *step_counter() const;
     uint32_t *ticket() const;  // of rd_launch_finish_reduce
     void launch_shape(StepArgs &a) const;
-    // keep: an even n leaves the buffers in the order they are in now (captured graphs)
-    rd_status launch_steps(double dt, int64_t n, bool keep = false);
+    rd_status launch_steps(double dt, int64_t n);
     rd_status step(double dt, int64_t n);
     // part < 0: every block; else the blocks of one part of a concatenated geometry
     rd_status balance(int s, double out[RD_NRED], int part = -1);

@@ -168,3 +168,44 @@ def test_adjoint_factor_states(rd, shape):
     for every in (2, 4, 9):
         got = run(every)
         assert got[0] == want[0] and np.array_equal(got[1], want[1]) and np.array_equal(got[2], want[2]), every
+
+
+# Direct launches inside a caller's own graph: an even number of steps leaves the two field
+# buffers as they were, so that each replay goes on from the last one.
+@pytest.mark.parametrize("factor", [False, True])
+@pytest.mark.parametrize("steps", [2, 4, 6])
+def test_callers_graph(rd, steps, factor):
+    import torch
+
+    shape = (24, 40, 33)
+    img = _image(shape, 0.8, 0.9)
+    rng = np.random.default_rng(6)
+    c0 = rng.random(shape, dtype=np.float32) * img
+    e = rng.random(shape, dtype=np.float32)
+
+    def sim(stream):
+        s = rd.Sim(rd.Geometry(img, None, 1.0, 8), "fp32")
+        s.add_species(1.0)
+        s.set_dirichlet(0, 1, 1.0)
+        s.set_kernel("column", 8)
+        s.set_launch(graph_steps=16, use_graph=False, xcd_map=False)
+        s.bind(features=rd.RD_WS_DIFFUSIVITY if factor else 0, stream=stream)
+        if factor:
+            s.set_diffusivity(e)
+        s.set_field(0, c0)
+        torch.cuda.synchronize()
+        return s
+
+    eager = sim(torch.cuda.current_stream())
+    side = torch.cuda.Stream()
+    s = sim(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        s.step(0.0625, steps)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        eager.step(0.0625, steps)
+        want = eager.get_field(0).cpu().numpy()
+        assert np.array_equal(s.get_field(0).cpu().numpy(), want)
+        torch.cuda.synchronize()
