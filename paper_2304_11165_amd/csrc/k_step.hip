@@ -1459,7 +1459,11 @@ int launch_fused_k(const StepArgs &a, int nsteps, int n_cu, hipStream_t st)
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, 0);
     if (e != hipSuccess) return (int)e;
     const int ngroups = (a.nb + 3) / 4;
-    int grid = per_cu * n_cu;                         // every workgroup resident
+    // Every workgroup resident.  The query counts vector registers and LDS; a wave may also
+    // hold up to 112 of a SIMD's 800 scalar registers, so that no more than 7 workgroups of
+    // four waves are sure to fit a CU (8 were allowed for kernels of 98 scalar registers, and
+    // the barrier of a grid of 1984 workgroups did not complete).
+    int grid = std::min(per_cu, 7) * n_cu;
     grid = std::min(grid, ((ngroups + 7) / 8) * 8);   // no more than the groups need
     grid = (grid / 8) * 8;
     if (grid < 8) return (int)hipErrorCooperativeLaunchTooLarge;

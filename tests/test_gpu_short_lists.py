@@ -79,3 +79,12 @@ def test_fp16_mixed_waves(rd, kernel):
         exact = c * (1.0 - 0.25 * 0.0625)
         gap = np.maximum(np.exp2(np.floor(np.log2(np.maximum(exact, 2.0 ** -30))) - 10), 2.0 ** -24)
         assert np.all(np.abs(got - exact) < gap * (1.0 + 2.0 ** -10))
+
+
+# More workgroups than seven per compute unit: a fused launch's grid stays within what is
+# resident at once, whatever scalar registers its kernel uses.
+def test_fused_grid_resident(rd):
+    img = np.ones((8, 8 * 89, 8 * 89), dtype=np.uint8)  # 1981 groups of four blocks
+    want = _run(rd, img, "fp32", 1, "persistent")
+    got = _run(rd, img, "fp32", 1, "column", 4)
+    assert np.array_equal(got[0], want[0])
