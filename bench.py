@@ -32,8 +32,8 @@ import time
 HBM_PEAK_GBS = 8000.0
 HERE = os.path.dirname(os.path.abspath(__file__))
 TRAFFIC_FILE = os.path.join(HERE, "profiles", "step_traffic.json")
-STEP_SOURCES = ["paper_2304_11165_amd/csrc/k_step.hip", "paper_2304_11165_amd/csrc/rd_device.h",
-                "paper_2304_11165_amd/csrc/rd_internal.h"]
+STEP_SOURCES = ["paper_2304_11165_amd/csrc/k_step.hip", "paper_2304_11165_amd/csrc/k_pair.hip",
+                "paper_2304_11165_amd/csrc/rd_device.h", "paper_2304_11165_amd/csrc/rd_internal.h"]
 METRIC = "active-voxel updates/s + achieved HBM GB/s (plain FP32 vs batched/BF16 form)"
 
 
@@ -206,6 +206,17 @@ def step_kernel_name(B, launch, S):
             "column_xch": "k_step8z<float,{S},true,{C},{D}>", "persistent": "k_step8p<float,{S},{D}>",
             "column_lanes": "k_step8l<float,{S},{D}>"}[kern]
     return name.format(S=S, C=cmp, D=d)
+
+
+def paired_kernel_name(B, launch, S, nb):
+    """HIP kernel that takes two FP32 steps per launch under a launch setting, or None (the
+    library's rule for the dithered FP32 steps of long block lists)."""
+    launch = launch or {}
+    if B != 8 or launch.get("layout") != "blocks" or launch.get("kernel") not in ("column", "column_xch"):
+        return None
+    if S > 2 or nb <= 1024:
+        return None
+    return "k_pair8z<float,true,false>" if S == 1 else "k_pair8z2<float,true>"
 
 
 def cg_words(prec):
@@ -793,7 +804,9 @@ def main():
         print(json.dumps({"profile": results}), flush=True)
         return
     f32 = results["fp32"]
-    kname = step_kernel_name(w.block_edge, f32["launch"], S)
+    paired = paired_kernel_name(w.block_edge, f32["launch"], S, nb)
+    kname = paired or step_kernel_name(w.block_edge, f32["launch"], S)
+    per_launch = 2 if paired else 1  # steps
     workload_name = f"soil{n}"
     traffic = load_traffic(a.traffic, kname, workload_name, f32["launch"]["xcd_map"])
     out = {
@@ -830,10 +843,11 @@ def main():
             "unit": "GB/s",
             "frac": f32["alg_GBps"] / HBM_PEAK_GBS,
             "traffic": traffic,
-            "alg_bytes_per_launch": f32["alg_bytes_per_launch"],
+            "steps_per_launch": per_launch,
+            "alg_bytes_per_launch": per_launch * f32["alg_bytes_per_launch"],
             "layout_GBps": f32["layout_GBps"],
-            "avg_launch_ms": f32["ms_per_step"],
-            "avg_launch_ms_stderr": f32["timing"]["ms_per_step_stderr"],
+            "avg_launch_ms": per_launch * f32["ms_per_step"],
+            "avg_launch_ms_stderr": per_launch * f32["timing"]["ms_per_step_stderr"],
         },
         "forms": results,
     }
