@@ -690,17 +690,11 @@ rd_status rd_sim::launch_steps(double dt, int64_t n)
         if (sr && n > 0) LAUNCHCHK(rd_launch_add_u32(step_counter(), (uint32_t)n, stream));
         return RD_OK;
     }
-    int64_t paired = pair_ok() || pair_diff_ok() ? n & ~(int64_t)1 : 0;  // the steps taken two per launch
-    if (paired & 2) {
-        // under capture (the library's own or a caller's) the number of launches stays even
-        // for an even n: a replay must find the buffers in the order they were captured in
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
-            (void)hipGetLastError();
-            cs = hipStreamCaptureStatusActive;
-        }
-        if (cs != hipStreamCaptureStatusNone) paired -= 2;
-    }
+    // The steps taken two per launch.  An even n makes an even number of launches, eager and
+    // under capture alike: the field ends in the buffer it started in, which a graph captured
+    // earlier (the library's own or a caller's) reads when it is replayed.
+    int64_t paired = pair_ok() || pair_diff_ok() ? n & ~(int64_t)1 : 0;
+    if (paired & 2) paired -= 2;
     for (int64_t i = 0; i < n; ++i) {
         StepArgs a = step_args(dt, cur);
         launch_shape(a);

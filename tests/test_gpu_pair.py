@@ -209,3 +209,48 @@ def test_callers_graph(rd, steps, factor):
         want = eager.get_field(0).cpu().numpy()
         assert np.array_equal(s.get_field(0).cpu().numpy(), want)
         torch.cuda.synchronize()
+
+
+# The same with eager work on the captured simulation itself between the replays: an even
+# number of steps leaves the buffers as they were eagerly, too (direct launches, a replayed
+# graph of the library with direct launches after it).
+@pytest.mark.parametrize("factor", [False, True])
+@pytest.mark.parametrize("captured,between", [(2, 2), (4, 6), (2, 18), (6, 22)])
+def test_replay_after_eager_steps(rd, captured, between, factor):
+    import torch
+
+    shape = (24, 40, 33)
+    img = _image(shape, 0.8, 0.9)
+    rng = np.random.default_rng(6)
+    c0 = rng.random(shape, dtype=np.float32) * img
+    e = rng.random(shape, dtype=np.float32)
+
+    def sim(stream, kernel):
+        s = rd.Sim(rd.Geometry(img, None, 1.0, 8), "fp32")
+        s.add_species(1.0)
+        s.set_dirichlet(0, 1, 1.0)
+        s.set_kernel(kernel, 8)
+        s.set_launch(graph_steps=16, use_graph=True, xcd_map=False)
+        s.bind(features=rd.RD_WS_DIFFUSIVITY if factor else 0, stream=stream)
+        if factor:
+            s.set_diffusivity(e)
+        s.set_field(0, c0)
+        torch.cuda.synchronize()
+        return s
+
+    single = sim(torch.cuda.current_stream(), "block")
+    side = torch.cuda.Stream()
+    s = sim(side, "column")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        s.step(0.0625, captured)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        s.step(0.0625, between)
+        torch.cuda.synchronize()
+        single.step(0.0625, captured + between)
+        want = single.get_field(0).cpu().numpy()
+        with torch.cuda.stream(side):  # the copy to the host waits for the simulation's stream
+            got = s.get_field(0).cpu().numpy()
+        assert np.array_equal(got, want)
