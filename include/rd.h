@@ -336,10 +336,10 @@ rd_status rd_sim_get_field(const rd_sim *sim, int species, float *dev_dense);
  * dt > 2 / lambda_max with the Gershgorin bound
  * lambda_max = 12 D_max/dx^2 + max_a(total rate out of a) + 6 max_a(k_R,a)/dx
  * (the 3-D form of the paper's eq. diffusion_stability_condition).
- * A simulation holds each field twice.  An even number of steps ends in the buffer it
- * started from and an odd number in the other one, for every launch setting: a caller who
- * captures an even number of steps into a graph of its own may replay it after any even
- * number of further steps with the same settings and workspace. */
+ * A simulation holds each field twice.  An even number of steps (an adjoint's included) ends
+ * in the buffer it started from and an odd number in the other one, for every launch setting:
+ * a caller who captures an even number of steps into a graph of its own may replay it after
+ * any even number of further steps with the same settings and workspace. */
 rd_status rd_sim_step(rd_sim *sim, double dt, int64_t n_steps);
 /* Steps taken since bind / the last set_field. */
 rd_status rd_sim_steps_taken(const rd_sim *sim, int64_t *n);

@@ -789,11 +789,12 @@ static rd_status adjoint_impl(rd_sim *sim, const float *dev_seed, int seed_mode,
     // segments of 20)
     for (int64_t j = 0; j < ncp; ++j) {
         const int64_t len = std::min<int64_t>(k, n_steps - j * k);
-        void *field = sim->field_ptr(sim->cur, 0);
-        HIPCHK(hipMemcpyAsync(slot(j), field, fbytes, hipMemcpyDeviceToDevice, stream));
+        HIPCHK(hipMemcpyAsync(slot(j), sim->field_ptr(sim->cur, 0), fbytes, hipMemcpyDeviceToDevice, stream));
         if (j < ncp - 1) {
             s = sim->step(dt, len);
         } else {
+            if (len & 1) sim->cur = 1 - sim->cur;  // as len steps of rd_sim_step leave it
+            void *field = sim->field_ptr(sim->cur, 0);
             s = run_states(len, [&](int64_t m) { return m == 0 ? slot(j) : m < len ? slot(ncp + m - 1) : field; });
             sim->steps_taken += len;
         }

@@ -254,3 +254,48 @@ def test_replay_after_eager_steps(rd, captured, between, factor):
         with torch.cuda.stream(side):  # the copy to the host waits for the simulation's stream
             got = s.get_field(0).cpu().numpy()
         assert np.array_equal(got, want)
+
+
+# An adjoint leaves the buffers as its number of steps does, whatever its segments: here 8
+# steps in segments of 5 (5 + 3), 3 (3 + 3 + 2) and 8.
+@pytest.mark.parametrize("factor", [False, True])
+@pytest.mark.parametrize("every", [3, 5, 8])
+def test_replay_after_adjoint(rd, every, factor):
+    import torch
+
+    shape = (24, 40, 33)
+    img = _image(shape, 0.8, 0.9)
+    rng = np.random.default_rng(6)
+    c0, target, e = (rng.random(shape, dtype=np.float32) * img for _ in range(3))
+    target = torch.as_tensor(target, device="cuda")
+
+    def sim(stream, kernel, features=0):
+        s = rd.Sim(rd.Geometry(img, None, 1.0, 8), "fp32")
+        s.add_species(1.0)
+        s.set_dirichlet(0, 1, 1.0)
+        s.set_kernel(kernel, 8)
+        s.bind(features=features | (rd.RD_WS_DIFFUSIVITY if factor else 0), stream=stream,
+               checkpoint_slots=-(-8 // every) + every - 1 if features else 0)
+        if factor:
+            s.set_diffusivity(e)
+        s.set_field(0, c0)
+        torch.cuda.synchronize()
+        return s
+
+    single = sim(torch.cuda.current_stream(), "block")
+    side = torch.cuda.Stream()
+    s = sim(side, "column", rd.RD_WS_ADJOINT)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        s.step(0.0625, 4)
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            s.adjoint(target, 8, 0.0625, every)
+        torch.cuda.synchronize()
+        single.step(0.0625, 4 + 8)
+        want = single.get_field(0).cpu().numpy()
+        with torch.cuda.stream(side):
+            got = s.get_field(0).cpu().numpy()
+        assert np.array_equal(got, want)
