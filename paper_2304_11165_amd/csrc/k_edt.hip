@@ -42,12 +42,21 @@ namespace {
 constexpr int EDT_FAR = 0x7fffffff;
 constexpr int EDT_ROWS = 8;  // rows of a tile, of its margins and of a far window
 
-// Workgroup id such that each XCD (consecutive workgroups go round-robin to the 8 of them)
-// walks one contiguous range of ids (gridDim.x is a multiple of 8, so a few come out past
-// the last one): the lines it reads are then shared in its own L2.
+// n workgroups in rows of at most 2^20, a multiple of 8: one dimension of a grid holds fewer
+// than 2^32 threads, and images of flat or thin shape (32768 x 1 x 32768) need more.
+constexpr int64_t EDT_GRID_ROW = 1 << 20;
+dim3 edt_grid(int64_t n)
+{
+    const int64_t row = n < EDT_GRID_ROW ? (n + 7) / 8 * 8 : EDT_GRID_ROW;
+    return dim3((unsigned)row, (unsigned)((n + row - 1) / row));
+}
+
+// Workgroup id of such a grid (a few come out past the last one) so that each XCD
+// (consecutive workgroups go round-robin to the 8 of them) walks one contiguous range of ids
+// in a row: the lines it reads are then shared in its own L2.
 __device__ __forceinline__ uint32_t xcd_range()
 {
-    return (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    return blockIdx.y * gridDim.x + (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
 }
 
 // The summary word of a wave's 64 words: the one nearest 0 if all are of one phase, else 0
@@ -66,7 +75,7 @@ __global__ __launch_bounds__(256) void k_edt_x(const uint8_t *__restrict__ img, 
                                                int *__restrict__ g, int *__restrict__ sum)
 {
     extern __shared__ uint64_t words[];  // 4 waves x chunks of 64 voxels
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t row = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (row >= nrows) return;  // whole waves; no workgroup barrier below
     const int nc = (nx + 63) / 64;
@@ -350,13 +359,12 @@ extern "C" rd_status rd_sdf_from_image(const uint8_t *dev_image, int64_t nx, int
     hipStream_t st = (hipStream_t)stream;
     const double diag = sqrt((double)nx * nx + (double)ny * ny + (double)nz * nz);
     const int64_t nc = (nx + 63) / 64;
-    auto grid8 = [](int64_t n) { return dim3((unsigned)((n + 7) / 8 * 8)); };  // as many for each XCD
-    hipLaunchKernelGGL(k_edt_x, dim3((unsigned)((ny * nz + 3) / 4)), dim3(256), 32 * (size_t)nc, st, dev_image, (int)nx,
+    hipLaunchKernelGGL(k_edt_x, edt_grid((ny * nz + 3) / 4), dim3(256), 32 * (size_t)nc, st, dev_image, (int)nx,
                        (int)ny, ny * nz, g, gsum);
-    hipLaunchKernelGGL(k_edt_y, grid8(nz * nc * ((ny + 31) / 32)), dim3(256), 0, st, g, gsum, (int)nx, (int)ny, (int)nz,
-                       (int)nc, h, hsum);
-    hipLaunchKernelGGL(k_edt_z, grid8(ny * nc * ((nz + 31) / 32)), dim3(256), 0, st, h, hsum, (int)nx, (int)ny, (int)nz,
-                       (int)nc, dx, diag, dev_sdf);
+    hipLaunchKernelGGL(k_edt_y, edt_grid(nz * nc * ((ny + 31) / 32)), dim3(256), 0, st, g, gsum, (int)nx, (int)ny,
+                       (int)nz, (int)nc, h, hsum);
+    hipLaunchKernelGGL(k_edt_z, edt_grid(ny * nc * ((nz + 31) / 32)), dim3(256), 0, st, h, hsum, (int)nx, (int)ny,
+                       (int)nz, (int)nc, dx, diag, dev_sdf);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return rd_fail(RD_ERR_HIP, std::string("EDT launch: ") + hipGetErrorString(e));
     return RD_OK;

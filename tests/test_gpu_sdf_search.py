@@ -42,3 +42,21 @@ def test_search_edges(rd, oracle_mod, shape, kind):
         got = rd.sdf_from_image(im, 0.7).cpu().numpy()
         want = oracle_mod.signed_distance(im, 0.7)
         assert np.array_equal(got, want)
+
+
+# Flat and thin images whose passes need 2^24 workgroups or more (2^32 threads, more than one
+# dimension of a grid holds), up to the limit of 32768 voxels an edge: planes of the other
+# phase 64 voxels apart, so that the distances are known.
+@pytest.mark.parametrize("shape,axis", [((32768, 1, 32768), 0), ((1, 32768, 32768), 1), ((8192, 8192, 1), 0)])
+def test_search_flat_images(rd, shape, axis):
+    import torch
+
+    img = torch.ones(shape, dtype=torch.uint8, device="cuda")
+    img.movedim(axis, 0)[::64] = 0
+    got = rd.sdf_from_image(img, 0.5)
+    k = torch.arange(shape[axis], device="cuda")
+    near = torch.minimum(k % 64, torch.where(k // 64 * 64 + 64 < shape[axis], 64 - k % 64, k))
+    want = torch.where(k % 64 == 0, -0.25, 0.5 * (near.double() - 0.5)).float()
+    want = want.reshape([-1 if a == axis else 1 for a in range(3)])
+    for z in range(0, shape[0], 4096):
+        assert bool((got[z : z + 4096] == (want[z : z + 4096] if axis == 0 else want)).all())
