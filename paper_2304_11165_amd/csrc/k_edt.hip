@@ -22,8 +22,9 @@
 // x 148 us, y 250 us, z 244 us, bound by vector instructions (4 + 4 bytes per voxel and
 // pass would take 80 us); one wave per row of 64 voxels and a load per candidate took
 // 888 / 643 us for y / z, envelope passes 2870 us each and twice (one per phase).  With
-// distances as long as the lines (512^3, one voxel of the other phase): 3.7 ms, against
-// 17.9 ms without the windows of edt_tile and 5.7 ms for the envelopes.
+// distances as long as the lines (512^3, one voxel of the other phase): 3.5 ms, against
+// 17.9 ms without the windows of edt_tile and 5.7 ms for the envelopes; 1024^3 17.2 and 34.0
+// ms, with 1e-3 of the voxels of the other phase 12.2 and 113 ms; 4096 x 4096 x 1 22.5 and 24.1.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -41,6 +42,12 @@ namespace {
 // longer than 32 would not fit any GPU.
 constexpr int EDT_FAR = 0x7fffffff;
 constexpr int EDT_ROWS = 8;  // rows of a tile, of its margins and of a far window
+// Lines up to EDT_LONG are searched by rows' summaries alone (RUNS = 0), longer ones also by
+// those of runs of 64 rows (1) and, above EDT_LONGER, of 512 (2).  ms with 0, 1 and 2 (512^3: 0
+// and 2): one voxel of the other phase in 512^3 3.5 / 1.9, 768^3 15.8 / 6.8 / 6.8, 1024^3 47.4
+// / 17.2 / 16.6; packed balls of an eighth of the edge 2.60 / 2.70, 8.6 / 8.8 / 8.9, 25.1 / 25.7 /
+// 26.0; one voxel in 4096 x 4096 x 1 to x 64 165 with 0, 22.6 with 2.
+constexpr int EDT_LONG = 512, EDT_LONGER = 2048;
 
 // n workgroups in rows of at most 2^20, a multiple of 8: one dimension of a grid holds fewer
 // than 2^32 threads, and images of flat or thin shape (32768 x 1 x 32768) need more.
@@ -161,9 +168,11 @@ struct EdtRows {
 // the summary word of row r.  The near candidates come from the tile and its two margins
 // (24 rows in registers, loaded once).  Farther away, windows of 8 rows are
 // read outward, each only if its summaries can still improve a voxel of the tile: across
-// a large void or solid that is one scalar load per 8 rows.
-__device__ __forceinline__ void edt_tile(const int *line, int64_t stride, const int *sum, int p0, int n, uint32_t x,
-                                         int out[EDT_ROWS])
+// a large void or solid that is one scalar load per 8 rows, or with RUNS one per 64 or 512
+// (c64: summaries of the line's rows in aligned runs of 64).
+template <int RUNS>
+__device__ __forceinline__ void edt_tile(const int *line, int64_t stride, const int *sum, const int *c64, int p0, int n,
+                                         uint32_t x, int out[EDT_ROWS])
 {
     constexpr int R = EDT_ROWS;
     EdtRows own, lo, hi;
@@ -195,6 +204,7 @@ __device__ __forceinline__ void edt_tile(const int *line, int64_t stride, const 
             if (t + k < 2 * R) best[t] = min(best[t], seen(t, t + k) + (uint32_t)(k * k));
         }
     }
+    int skip[2] = {0, 0};  // RUNS: rows nearer than this are known not to help, below and above
     for (int k0 = R + 1;; k0 += R) {
         const int e = p0 + 1 - k0, b = p0 + R - 1 + k0;  // rows below e and from b on are not seen yet
         if (e <= 0 && b >= n) break;
@@ -205,16 +215,38 @@ __device__ __forceinline__ void edt_tile(const int *line, int64_t stride, const 
             mi = max(mi, act[t] ? 0u : best[t]);
         }
         if (!__any(max(ma, mi) > (uint32_t)(k0 * k0))) break;
+        // RUNS: no row with one of these summaries, at least k0 away, improves a voxel of the tile
+        auto useless = [&](const int *w, int count) {
+            int sa = EDT_FAR, si = EDT_FAR;
+#pragma unroll
+            for (int s = 0; s < count; ++s) {
+                sa = min(sa, max(w[s], 0));
+                si = min(si, max(-w[s], 0));
+            }
+            return !__any(ma > (uint32_t)sa + (uint32_t)(k0 * k0) || mi > (uint32_t)si + (uint32_t)(k0 * k0));
+        };
 #pragma unroll
         for (int dir = 0; dir < 2; ++dir) {
             if (dir ? b >= n : e <= 0) continue;
+            if constexpr (RUNS > 0) {
+                if (k0 < skip[dir]) continue;
+                const int row = dir ? b : e, r64 = dir ? row >> 6 : (row >> 6) - 1, n64 = (n + 63) >> 6;
+                if (RUNS > 1 && (row & 511) == 0 && useless(c64 + (dir ? min(r64, n64 - R) : r64 - (R - 1)), R)) {
+                    skip[dir] = k0 + 512;
+                    continue;
+                }
+                if ((row & 63) == 0 && useless(c64 + r64, 1)) {
+                    skip[dir] = k0 + 64;
+                    continue;
+                }
+            }
             const int r0 = dir ? min(b, n - R) : max(e - R, 0);  // n > R here
             int sa = EDT_FAR, si = EDT_FAR;
 #pragma unroll
             for (int s = 0; s < R; ++s) {
-                const int w = sum[r0 + s];
-                sa = min(sa, max(w, 0));
-                si = min(si, max(-w, 0));
+                const int v = sum[r0 + s];
+                sa = min(sa, max(v, 0));
+                si = min(si, max(-v, 0));
             }
             if (!__any(ma > (uint32_t)sa + (uint32_t)(k0 * k0) || mi > (uint32_t)si + (uint32_t)(k0 * k0))) continue;
             EdtRows w;
@@ -231,14 +263,35 @@ __device__ __forceinline__ void edt_tile(const int *line, int64_t stride, const 
                 }
             }
         }
+        if constexpr (RUNS > 0) k0 = max(k0, min(e > 0 ? skip[0] : n, b < n ? skip[1] : n) - R);
     }
 #pragma unroll
     for (int t = 0; t < R; ++t) out[t] = act[t] ? (int)best[t] : -(int)best[t];
 }
 
+// Summaries of the aligned runs of 64 rows of every line from those of its n rows, four per wave.
+__global__ __launch_bounds__(256) void k_edt_runs(const int *__restrict__ sum, int n, int64_t nlines,
+                                                  int *__restrict__ c64)
+{
+    const int n64 = (n + 63) / 64, n256 = (n + 255) / 256, lane = threadIdx.x & 63;
+    const int64_t wave = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6), l = wave / n256;
+    if (l >= nlines) return;
+    const int r0 = (int)(wave % n256) * 4;
+    int w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = (r0 + k) * 64 + lane < n ? sum[l * n + (r0 + k) * 64 + lane] : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int v = edt_summary(w[k], (r0 + k) * 64 + lane < n);
+        if (lane == 0 && r0 + k < n64) c64[l * n64 + r0 + k] = v;
+    }
+}
+
 // Four tiles of one 64-voxel column block of a plane per workgroup.
-__global__ __launch_bounds__(256) void k_edt_y(const int *__restrict__ g, const int *__restrict__ gsum, int nx, int ny,
-                                               int nz, int nc, int *__restrict__ h, int *__restrict__ hsum)
+template <int RUNS>
+__global__ __launch_bounds__(256) void k_edt_y(const int *__restrict__ g, const int *__restrict__ gsum,
+                                               const int *__restrict__ c64, int nx, int ny, int nz, int nc,
+                                               int *__restrict__ h, int *__restrict__ hsum)
 {
     const uint32_t wg = xcd_range(), nt = (uint32_t)(ny + 31) / 32;
     const int c = (int)(wg / nt % (uint32_t)nc), z = (int)(wg / nt / (uint32_t)nc);
@@ -248,7 +301,9 @@ __global__ __launch_bounds__(256) void k_edt_y(const int *__restrict__ g, const 
     const bool in = c * 64 + lane < nx;
     const uint32_t x = (uint32_t)min(c * 64 + lane, nx - 1);
     int w[EDT_ROWS];
-    edt_tile(g + (int64_t)z * ny * nx, nx, gsum + ((int64_t)z * nc + c) * ny, y0, ny, x, w);
+    const int64_t l = (int64_t)z * nc + c;
+    edt_tile<RUNS>(g + (int64_t)z * ny * nx, nx, gsum + l * ny, c64 + l * ((ny + 63) / 64), y0, ny,
+                   x, w);
     int *out = h + ((int64_t)z * ny + y0) * nx;
 #pragma unroll
     for (int t = 0; t < EDT_ROWS; ++t) {
@@ -260,8 +315,10 @@ __global__ __launch_bounds__(256) void k_edt_y(const int *__restrict__ g, const 
 }
 
 // Four tiles of one 64-voxel piece of a row through the planes per workgroup.
-__global__ __launch_bounds__(256) void k_edt_z(const int *__restrict__ h, const int *__restrict__ hsum, int nx, int ny,
-                                               int nz, int nc, double dx, double diag, float *__restrict__ sdf)
+template <int RUNS>
+__global__ __launch_bounds__(256) void k_edt_z(const int *__restrict__ h, const int *__restrict__ hsum,
+                                               const int *__restrict__ c64, int nx, int ny, int nz, int nc,
+                                               double dx, double diag, float *__restrict__ sdf)
 {
     const uint32_t wg = xcd_range(), nt = (uint32_t)(nz + 31) / 32;
     const int c = (int)(wg / nt % (uint32_t)nc), y = (int)(wg / nt / (uint32_t)nc);
@@ -272,7 +329,9 @@ __global__ __launch_bounds__(256) void k_edt_z(const int *__restrict__ h, const 
     const uint32_t x = (uint32_t)min(c * 64 + lane, nx - 1);
     const int64_t plane = (int64_t)ny * nx;
     int w[EDT_ROWS];
-    edt_tile(h + (int64_t)y * nx, plane, hsum + ((int64_t)y * nc + c) * nz, z0, nz, x, w);
+    const int64_t l = (int64_t)y * nc + c;
+    edt_tile<RUNS>(h + (int64_t)y * nx, plane, hsum + l * nz, c64 + l * ((nz + 63) / 64), z0, nz, x,
+                   w);
     float *out = sdf + z0 * plane + (int64_t)y * nx;
 #pragma unroll
     for (int t = 0; t < EDT_ROWS; ++t) {
@@ -361,10 +420,23 @@ extern "C" rd_status rd_sdf_from_image(const uint8_t *dev_image, int64_t nx, int
     const int64_t nc = (nx + 63) / 64;
     hipLaunchKernelGGL(k_edt_x, edt_grid((ny * nz + 3) / 4), dim3(256), 32 * (size_t)nc, st, dev_image, (int)nx,
                        (int)ny, ny * nz, g, gsum);
-    hipLaunchKernelGGL(k_edt_y, edt_grid(nz * nc * ((ny + 31) / 32)), dim3(256), 0, st, g, gsum, (int)nx, (int)ny,
-                       (int)nz, (int)nc, h, hsum);
-    hipLaunchKernelGGL(k_edt_z, edt_grid(ny * nc * ((nz + 31) / 32)), dim3(256), 0, st, h, hsum, (int)nx, (int)ny,
-                       (int)nz, (int)nc, dx, diag, dev_sdf);
+    // the summaries of runs, behind those of the z pass's rows (their words are 2 % of these);
+    // the y pass has read its own when the z pass's are written
+    int *c64 = hsum + align256(4 * (size_t)(ny * nc * nz)) / 4;
+    auto runs = [&](const int *sum, int64_t n, int64_t nlines) {  // the form of the line pass
+        if (n <= EDT_LONG) return 0;
+        hipLaunchKernelGGL(k_edt_runs, edt_grid((nlines * ((n + 255) / 256) + 3) / 4), dim3(256), 0, st, sum, (int)n,
+                           nlines, c64);
+        return n <= EDT_LONGER ? 1 : 2;
+    };
+    int form = runs(gsum, ny, nz * nc);
+    hipLaunchKernelGGL((form == 0 ? k_edt_y<0> : form == 1 ? k_edt_y<1> : k_edt_y<2>),
+                       edt_grid(nz * nc * ((ny + 31) / 32)), dim3(256), 0, st, g, gsum, c64, (int)nx, (int)ny, (int)nz,
+                       (int)nc, h, hsum);
+    form = runs(hsum, nz, ny * nc);
+    hipLaunchKernelGGL((form == 0 ? k_edt_z<0> : form == 1 ? k_edt_z<1> : k_edt_z<2>),
+                       edt_grid(ny * nc * ((nz + 31) / 32)), dim3(256), 0, st, h, hsum, c64, (int)nx, (int)ny, (int)nz,
+                       (int)nc, dx, diag, dev_sdf);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return rd_fail(RD_ERR_HIP, std::string("EDT launch: ") + hipGetErrorString(e));
     return RD_OK;

@@ -60,3 +60,19 @@ def test_search_flat_images(rd, shape, axis):
     want = want.reshape([-1 if a == axis else 1 for a in range(3)])
     for z in range(0, shape[0], 4096):
         assert bool((got[z : z + 4096] == (want[z : z + 4096] if axis == 0 else want)).all())
+
+
+# Lines searched with summaries of 64 and 512 rows: lengths around their multiples, both axes,
+# features at the ends, in the middle and hundreds of rows apart.
+@pytest.mark.parametrize("kind", ["corner", "two", "half", "sparse", "far"])
+@pytest.mark.parametrize("n", [513, 575, 577, 1024, 1031, 2049])
+def test_search_long_lines(rd, oracle_mod, n, kind):
+    for shape in ((n, 3, 70), (2, n, 9), (n, n // 8 + 1, 1)):
+        if kind == "far":
+            img = np.ones(shape, np.uint8)
+            img.flat[np.random.default_rng(n).integers(0, img.size, 5)] = 0
+        else:
+            img = _image(shape, kind)
+        for im in (img, 1 - img):
+            got = rd.sdf_from_image(im, 0.7).cpu().numpy()
+            assert np.array_equal(got, oracle_mod.signed_distance(im, 0.7)), shape
