@@ -219,6 +219,14 @@ def paired_kernel_name(B, launch, S, nb):
     return "k_pair8z<float,true,false>" if S == 1 else "k_pair8z2<float,true>"
 
 
+def timed_kernel(B, launch, S, nb, chunk):
+    """(HIP kernel, steps per launch) of FP32 steps timed in chunks of `chunk` steps.  The
+    library keeps the number of launches even for an even number of steps, so only chunks of
+    a multiple of 4 consist of pairs; any other is named by its single steps."""
+    paired = paired_kernel_name(B, launch, S, nb) if chunk % 4 == 0 else None
+    return (paired, 2) if paired else (step_kernel_name(B, launch, S), 1)
+
+
 def cg_words(prec):
     """Vector words per active voxel and CG iteration: the matvec with the p update fused
     (reads p and z, or r without the preconditioner; writes p) and the x, r update with
@@ -804,9 +812,7 @@ def main():
         print(json.dumps({"profile": results}), flush=True)
         return
     f32 = results["fp32"]
-    paired = paired_kernel_name(w.block_edge, f32["launch"], S, nb)
-    kname = paired or step_kernel_name(w.block_edge, f32["launch"], S)
-    per_launch = 2 if paired else 1  # steps
+    kname, per_launch = timed_kernel(w.block_edge, f32["launch"], S, nb, f32["timing"]["steps_per_chunk"])
     workload_name = f"soil{n}"
     traffic = load_traffic(a.traffic, kname, workload_name, f32["launch"]["xcd_map"])
     out = {

@@ -55,3 +55,16 @@ def test_committed_traffic_records_well_formed():
 ])
 def test_step_kernel_names(launch, name):
     assert bench.step_kernel_name(8, launch, 2) == name
+
+
+# The line names the kernel of the chunks that were timed: pairs only where a chunk is a
+# multiple of 4 steps (20 steps are timed as single steps, long runs as graphs of 16 or 64).
+@pytest.mark.parametrize("chunk,steps", [(1, 1), (2, 1), (6, 1), (10, 1), (4, 2), (16, 2), (64, 2)])
+@pytest.mark.parametrize("layout", ["blocks", "compact"])
+def test_timed_kernel_follows_the_chunks(chunk, steps, layout):
+    launch = {"kernel": "column_xch", "layout": layout}
+    name, per_launch = bench.timed_kernel(8, launch, 2, 147730, chunk)
+    if layout == "compact" or steps == 1:
+        assert (name, per_launch) == (bench.step_kernel_name(8, launch, 2), 1)
+    else:
+        assert (name, per_launch) == ("k_pair8z2<float,true>", 2)
