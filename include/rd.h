@@ -454,7 +454,8 @@ rd_status rd_sim_autotune(rd_sim *sim, double dt, int64_t trial_steps, double *b
 /* rd_sim_autotune with a result cache, for callers that bind the same geometry again
  * and should not pay the trials every time.  The key
  * covers the GPU (architecture and compute units), storage type, species count,
- * reactions, Robin walls and the geometry (extents, block edge, every activity word).
+ * reactions, Robin walls, stochastic rounding, a diffusivity factor, an active sink band,
+ * the library's step kernels and the geometry (extents, block edge, every activity word).
  * A cache hit applies the stored launch configuration without trials and leaves the
  * fields untouched; a miss runs rd_sim_autotune (which resets the fields) and appends
  * one text line "rdtune1 <key> <kernel> <xcd> <graph> <wg_per_cu> <graph_steps> <ms>" to

@@ -1161,9 +1161,15 @@ extern "C" rd_status rd_sim_autotune(rd_sim *sim, double dt, int64_t trial_steps
 }
 
 namespace {
+// Kernels that a launch setting stands for: raised when another setting may have become the
+// fastest, so that results stored with earlier ones are tuned anew (2: steps in pairs, short
+// lists by the workgroup kernel, block order in runs).
+constexpr int TUNE_KERNELS = 2;
+
 // Key of an autotuning result: the GPU (architecture name and compute-unit count), the
-// storage type, species, reactions and Robin walls, and the geometry (extents, block edge,
-// every activity mask word), folded with FNV-1a 64.
+// storage type, species, reactions and Robin walls, what else decides which kernel a setting
+// launches (rounding, a diffusivity factor, an active sink band), and the geometry (extents,
+// block edge, every activity mask word), folded with FNV-1a 64.
 uint64_t tune_key(const rd_sim *sim)
 {
     uint64_t h = 1469598103934665603ull;
@@ -1183,7 +1189,8 @@ uint64_t tune_key(const rd_sim *sim)
     const rd_geometry &g = *sim->g;
     const int64_t dims[5] = {g.nx, g.ny, g.nz, (int64_t)g.B, g.nb()};
     mix(dims, sizeof(dims));
-    const int meta[4] = {(int)sim->storage, sim->S, (int)sim->reactions.size(), sim->compact ? 1 : 0};
+    const int meta[8] = {(int)sim->storage, sim->S, (int)sim->reactions.size(), sim->compact ? 1 : 0,
+                         sim->sround ? 1 : 0, sim->diff_on ? 1 : 0, sim->sink_active() ? 1 : 0, TUNE_KERNELS};
     mix(meta, sizeof(meta));
     for (int s = 0; s < sim->S; ++s) {
         const int robin = sim->robin[s] != 0.0;
