@@ -1450,6 +1450,16 @@ int rd_launch_step(int storage, int B, const StepArgs &a, void *stream)
     RD_DISPATCH(storage, B, launch_step_t, a, (hipStream_t)stream);
 }
 
+// Every workgroup resident.  The occupancy query (per_cu) counts vector registers and LDS; a
+// wave may also hold up to 112 of a SIMD's 800 scalar registers, so that no more than 7
+// workgroups of four waves are sure to fit a CU (8 were allowed for kernels of 98 scalar
+// registers, and the barrier of a grid of 1984 workgroups did not complete).
+int rd_fused_grid(int per_cu, int n_cu, int ngroups)
+{
+    const int grid = std::min(std::min(per_cu, 7) * n_cu, ((ngroups + 7) / 8) * 8);  // no more than the groups need
+    return grid / 8 * 8;
+}
+
 namespace {
 template <typename T, int S, bool XCH, bool DTH>
 int launch_fused_k(const StepArgs &a, int nsteps, int n_cu, hipStream_t st)
@@ -1459,13 +1469,7 @@ int launch_fused_k(const StepArgs &a, int nsteps, int n_cu, hipStream_t st)
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, 0);
     if (e != hipSuccess) return (int)e;
     const int ngroups = (a.nb + 3) / 4;
-    // Every workgroup resident.  The query counts vector registers and LDS; a wave may also
-    // hold up to 112 of a SIMD's 800 scalar registers, so that no more than 7 workgroups of
-    // four waves are sure to fit a CU (8 were allowed for kernels of 98 scalar registers, and
-    // the barrier of a grid of 1984 workgroups did not complete).
-    int grid = std::min(per_cu, 7) * n_cu;
-    grid = std::min(grid, ((ngroups + 7) / 8) * 8);   // no more than the groups need
-    grid = (grid / 8) * 8;
+    const int grid = rd_fused_grid(per_cu, n_cu, ngroups);
     if (grid < 8) return (int)hipErrorCooperativeLaunchTooLarge;
     StepArgs args = a;
     int ns = nsteps;

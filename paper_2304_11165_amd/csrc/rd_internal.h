@@ -160,6 +160,8 @@ int rd_launch_fill_u32(void *ptr, uint32_t value, int64_t n_words, void *stream)
 // launch (grid barrier between steps); the buffers swap after each step, as in nsteps
 // single-step launches; a.ctr_off is the first step's offset.  n_cu: compute units.
 int rd_launch_step_fused(int storage, const StepArgs &a, int nsteps, int n_cu, void *stream);
+// its workgroups: a multiple of 8 that is resident at once (0: fewer than 8 are)
+int rd_fused_grid(int per_cu, int n_cu, int ngroups);
 // compact layout: the halo records (StepArgs::hrec) of nb blocks
 int rd_launch_halo_rec8(const BlockInfo *info, const uint64_t *mask, const uint32_t *cbase, uint32_t *hrec,
                         int nb, void *stream);
