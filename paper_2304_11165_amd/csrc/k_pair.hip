@@ -385,7 +385,11 @@ __global__ __launch_bounds__(256, 5) void k_pair8z2(StepArgs a)
 }
 // One species with the factor: 32 KB of LDS per workgroup.  us per step, k_step8e without and
 // with the x-face exchange / a pair: FP32 packing 64^3 5.1, 6.2 / 4.1, 160^3 14.8, 16.2 / 12.3,
-// soil 256^3 25.1, 28.1 / 21.9; BF16 with stochastic rounding 160^3 14.4, 14.8 / 13.3.
+// soil 256^3 25.1, 28.1 / 21.9; BF16 with stochastic rounding 160^3 14.4, 14.8 / 13.3.  Lists
+// of 216, 1000, 2744 and 7996 blocks, without the exchange / a pair: FP32 5.1 / 4.0, 5.2 / 4.1, 7.2 /
+// 5.4, 15.5 / 11.9; BF16 5.3 / 4.0, 5.3 / 4.1, 7.2 / 5.4, 13.1 / 11.1, with stochastic rounding
+// 5.6 / 4.5, 5.6 / 4.6, 7.6 / 6.3, 14.2 / 12.7; FP16 as BF16, with it 6.0 / 5.1, 5.9 / 5.1, 8.1 /
+// 7.0, 15.1 / 14.2.
 template <typename T, bool SR, bool MID>
 __global__ __launch_bounds__(256, 5) void k_pair8e(StepArgs a, const float *e)
 {

@@ -1557,9 +1557,10 @@ int launch_scatter_t(const BlockInfo *info, const uint64_t *mask, const uint32_t
         hipLaunchKernelGGL((few ? k_scatter8<T, 2> : k_scatter8<T, 8>), dim3(rd_xcd_grid(groups, order)), dim3(256), 0,
                            st, info, mask, cbase, geom, nb, order, dense, (T *)field, dir, dv[0], dv[1], dv[2], dv[3],
                            dv[4], dv[5]);
-    } else
-    hipLaunchKernelGGL((k_scatter<T, B>), dim3(nb), dim3(256), 0, st, info, mask, cbase, geom, nb, dense,
-                       (T *)field, dir, dv[0], dv[1], dv[2], dv[3], dv[4], dv[5]);
+    } else {
+        hipLaunchKernelGGL((k_scatter<T, B>), dim3(nb), dim3(256), 0, st, info, mask, cbase, geom, nb, dense,
+                           (T *)field, dir, dv[0], dv[1], dv[2], dv[3], dv[4], dv[5]);
+    }
     return (int)hipGetLastError();
 }
 template <typename T, int B>
@@ -1571,9 +1572,10 @@ int launch_gather_t(const BlockInfo *info, const uint64_t *mask, const uint32_t 
         const int groups = few ? nb : (nb + 3) / 4, order = rd_xcd_order(groups, false);
         hipLaunchKernelGGL((few ? k_gather8<T, 2> : k_gather8<T, 8>), dim3(rd_xcd_grid(groups, order)), dim3(256), 0,
                            st, info, mask, cbase, geom, nb, order, (const T *)field, dense);
-    } else
-    hipLaunchKernelGGL((k_gather<T, B>), dim3(nb), dim3(256), 0, st, info, mask, cbase, geom, nb,
-                       (const T *)field, dense);
+    } else {
+        hipLaunchKernelGGL((k_gather<T, B>), dim3(nb), dim3(256), 0, st, info, mask, cbase, geom, nb,
+                           (const T *)field, dense);
+    }
     return (int)hipGetLastError();
 }
 }  // namespace

@@ -620,7 +620,9 @@ uint32_t *rd_sim::ticket() const { return (uint32_t *)(ws + L.res + 448); }
 // block, packings of 64^3, 80^3, 96^3 (505, 989, 1710 blocks): one species FP32 4.0 / 3.3,
 // 4.1 / 3.7, 4.4 / 4.5; two species FP32 4.8 / 3.7, 5.1 / 4.3, 5.9 / 5.4, BF16 with
 // stochastic rounding 5.6 / 4.2, 5.7 / 4.8, 6.6 / 6.1; 112^3 (2714) two species 7.0 / 6.8,
-// BF16 7.8 / 8.2.
+// BF16 7.8 / 8.2.  Three and four species on lists of 216, 1000 and 1728 blocks: FP32 5.8 /
+// 3.7, 6.2 / 5.0, 7.1 / 5.8 and 7.0 / 4.0, 7.2 / 5.5, 9.4 / 7.6, FP16 with stochastic rounding
+// 7.2 / 4.4, 7.3 / 5.4, 8.4 / 7.0 and 8.8 / 4.7, 8.8 / 6.0, 10.4 / 7.9.
 int rd_sim::step_kernel() const
 {
     if (g->B != 8) return 0;
@@ -663,7 +665,7 @@ bool rd_sim::pair_ok() const
 }
 
 // With a diffusivity factor a pair of one species' steps is the faster form at every length
-// measured (64 to 18 071 blocks, figures at k_pair8e).
+// measured (64 to 18 071 blocks) in every storage type and rounding (figures at k_pair8e).
 bool rd_sim::pair_diff_ok() const
 {
     return g->B == 8 && !compact && (kernel == 2 || kernel == 3) && S == 1 && diff_on && !sink_active();

@@ -97,8 +97,8 @@ struct rd_sim {
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;
     std::vector<GeomInfo> geom_host;  // one entry per part (the device copy's source)
-    double *host_res = nullptr;  // pinned; kernels write results to it (host_dev)
-    double *host_res_dev = nullptr;
+    double *host_res = nullptr;      // pinned; kernels write results to it
+    double *host_res_dev = nullptr;  // its device address
     std::vector<GraphEntry> graphs;
 
     int cur = 0;  // buffer holding the current field
