@@ -220,9 +220,9 @@ def paired_kernel_name(B, launch, S, nb):
 
 
 def timed_kernel(B, launch, S, nb, chunk):
-    """(HIP kernel, steps per launch) of FP32 steps timed in chunks of `chunk` steps.  The
-    library keeps the number of launches even for an even number of steps, so only chunks of
-    a multiple of 4 consist of pairs; any other is named by its single steps."""
+    """(HIP kernel, steps per launch) of FP32 steps timed in chunks of `chunk` steps (single
+    steps or captured graphs).  The library keeps a graph's number of launches even, so only
+    graphs of a multiple of 4 steps consist of pairs; any other is named by its single steps."""
     paired = paired_kernel_name(B, launch, S, nb) if chunk % 4 == 0 else None
     return (paired, 2) if paired else (step_kernel_name(B, launch, S), 1)
 

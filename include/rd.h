@@ -222,10 +222,10 @@ rd_status rd_sim_set_layout(rd_sim *sim, int layout);
  *               exchanged between lanes (DPP row shifts, ds_bpermute) instead of an
  *               LDS tile.
  * Results are bitwise identical.  Kernels 2 and 3 take two steps per launch where that is
- * faster (block layout, one or two species) and leave short block lists to kernel 0.  The
- * number of launches stays even for an even number of steps, so such a run (and a captured
- * graph) is taken wholly in pairs if it is a multiple of 4 steps; of any other length the
- * last one to three steps are launched singly.
+ * faster (block layout, one or two species) and leave short block lists to kernel 0.  A
+ * graph (rd_sim_set_launch, or a caller's) keeps an even number of launches, so it consists
+ * of pairs if it is a multiple of 4 steps; of any other length its last one to three steps
+ * are launched singly.
  * RD_ERR_ARG for kernel outside 0..4 or wg_per_cu
  * outside 1..32; RD_ERR_STATE for kernel 0 or 1 with the compact layout and for
  * kernel 4 with the block layout. */
@@ -336,10 +336,11 @@ rd_status rd_sim_get_field(const rd_sim *sim, int species, float *dev_dense);
  * dt > 2 / lambda_max with the Gershgorin bound
  * lambda_max = 12 D_max/dx^2 + max_a(total rate out of a) + 6 max_a(k_R,a)/dx
  * (the 3-D form of the paper's eq. diffusion_stability_condition).
- * A simulation holds each field twice.  An even number of steps (an adjoint's included) ends
- * in the buffer it started from and an odd number in the other one, for every launch setting:
- * a caller who captures an even number of steps into a graph of its own may replay it after
- * any even number of further steps with the same settings and workspace. */
+ * Callers may capture rd_sim_step of an even number of steps, rd_sim_set_field and
+ * rd_sim_get_field into graphs of their own on the bound stream and replay them with the
+ * same settings and workspace, also after further even numbers of steps (an adjoint's
+ * included): a simulation holds each field twice, and from its first captured call on an
+ * even number of steps ends in the buffer it started from, for every launch setting. */
 rd_status rd_sim_step(rd_sim *sim, double dt, int64_t n_steps);
 /* Steps taken since bind / the last set_field. */
 rd_status rd_sim_steps_taken(const rd_sim *sim, int64_t *n);

@@ -538,6 +538,7 @@ rd_status rd_sim::upload(bool index)
 rd_status rd_sim::apply_dirichlet(int s)
 {
     if (!ws || !dir[s]) return RD_OK;
+    note_capture();
     float dv[6];
     for (int f = 0; f < 6; ++f) dv[f] = (float)dirval[s][f];
     LAUNCHCHK(rd_launch_set_dirichlet(storage, g->B, (const BlockInfo *)(ws + L.info),
@@ -671,6 +672,19 @@ bool rd_sim::pair_diff_ok() const
     return g->B == 8 && !compact && (kernel == 2 || kernel == 3) && S == 1 && diff_on && !sink_active();
 }
 
+// Called where a kernel is given the current buffer's address: from the first time that this
+// happens under a caller's capture, a graph may hold that address.
+void rd_sim::note_capture() const
+{
+    if (caller_graph || own_capture()) return;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {  // the null stream beside a capture
+        (void)hipGetLastError();
+        cs = hipStreamCaptureStatusActive;
+    }
+    caller_graph = cs != hipStreamCaptureStatusNone;
+}
+
 rd_status rd_sim::launch_steps(double dt, int64_t n)
 {
     // stochastic rounding: at the store for 16-bit storage; for FP32 storage a dither of
@@ -692,11 +706,14 @@ rd_status rd_sim::launch_steps(double dt, int64_t n)
         if (sr && n > 0) LAUNCHCHK(rd_launch_add_u32(step_counter(), (uint32_t)n, stream));
         return RD_OK;
     }
-    // The steps taken two per launch.  An even n makes an even number of launches, eager and
-    // under capture alike: the field ends in the buffer it started in, which a graph captured
-    // earlier (the library's own or a caller's) reads when it is replayed.
+    // The steps taken two per launch.  Where a graph may be replayed (the library's own that is
+    // being captured, or a caller's) an even n makes an even number of launches: the field ends
+    // in the buffer it started in, which is the one the graph reads.  Otherwise nothing outside
+    // sees which buffer holds the field, and 10 steps are five pairs (soil 256^3 213 us, as four
+    // pairs and two single steps 230).
+    note_capture();
     int64_t paired = pair_ok() || pair_diff_ok() ? n & ~(int64_t)1 : 0;
-    if (paired & 2) paired -= 2;
+    if ((paired & 2) && (caller_graph || own_capture())) paired -= 2;
     for (int64_t i = 0; i < n; ++i) {
         StepArgs a = step_args(dt, cur);
         launch_shape(a);
@@ -858,6 +875,7 @@ extern "C" rd_status rd_sim_set_field(rd_sim *sim, int species, const float *dev
     if (!dev_dense) return rd_fail(RD_ERR_ARG, "field pointer is NULL");
     float dv[6];
     for (int f = 0; f < 6; ++f) dv[f] = (float)sim->dirval[species][f];
+    sim->note_capture();
     LAUNCHCHK(rd_launch_scatter(sim->storage, sim->g->B, (const BlockInfo *)(sim->ws + sim->L.info),
                                 (const uint64_t *)(sim->ws + sim->L.mask), sim->cbase_ptr(),
                                 (const GeomInfo *)(sim->ws + sim->L.geom), (int)sim->g->nb(),
@@ -984,6 +1002,7 @@ extern "C" rd_status rd_sim_get_field(const rd_sim *sim, int species, float *dev
     if (species < 0 || species >= sim->S) return rd_fail(RD_ERR_ARG, "bad species");
     if (!dev_dense) return rd_fail(RD_ERR_ARG, "field pointer is NULL");
     const rd_geometry &G = *sim->g;
+    sim->note_capture();
     LAUNCHCHK(rd_launch_gather(sim->storage, G.B, (const BlockInfo *)(sim->ws + sim->L.info),
                                (const uint64_t *)(sim->ws + sim->L.mask), sim->cbase_ptr(),
                                (const GeomInfo *)(sim->ws + sim->L.geom), (int)G.nb(),

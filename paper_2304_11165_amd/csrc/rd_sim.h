@@ -102,6 +102,11 @@ struct rd_sim {
     std::vector<GraphEntry> graphs;
 
     int cur = 0;  // buffer holding the current field
+    // a caller has captured calls of this simulation (which may be replayed at any time): an
+    // even number of steps then leaves `cur` as it was
+    mutable bool caller_graph = false;
+    void note_capture() const;
+    bool own_capture() const { return cap_stream && stream == cap_stream; }  // in rd_sim_step
     int64_t steps_taken = 0;
 
     ~rd_sim();

@@ -213,7 +213,7 @@ def test_callers_graph(rd, steps, factor):
 
 # The same with eager work on the captured simulation itself between the replays: an even
 # number of steps leaves the buffers as they were eagerly, too (direct launches, a replayed
-# graph of the library with direct launches after it).
+# graph of the library with direct launches after it), from the capture on.
 @pytest.mark.parametrize("factor", [False, True])
 @pytest.mark.parametrize("captured,between", [(2, 2), (4, 6), (2, 18), (6, 22)])
 def test_replay_after_eager_steps(rd, captured, between, factor):
@@ -241,6 +241,10 @@ def test_replay_after_eager_steps(rd, captured, between, factor):
     single = sim(torch.cuda.current_stream(), "block")
     side = torch.cuda.Stream()
     s = sim(side, "column")
+    for n in (2, 1):
+        s.step(0.0625, n)
+        single.step(0.0625, n)
+    torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=side):
         s.step(0.0625, captured)
@@ -299,3 +303,48 @@ def test_replay_after_adjoint(rd, every, factor):
         with torch.cuda.stream(side):
             got = s.get_field(0).cpu().numpy()
         assert np.array_equal(got, want)
+
+
+# A captured copy of the field (or into it) holds the buffer's address as captured steps do.
+@pytest.mark.parametrize("call", ["get", "set"])
+@pytest.mark.parametrize("between", [2, 6, 18])
+def test_replay_of_copies(rd, between, call):
+    import torch
+
+    shape = (24, 40, 33)
+    img = _image(shape, 0.8, 0.9)
+    rng = np.random.default_rng(6)
+    c0, c1 = (torch.as_tensor(rng.random(shape, dtype=np.float32) * img, device="cuda") for _ in range(2))
+
+    def sim(stream, kernel):
+        s = rd.Sim(rd.Geometry(img, None, 1.0, 8), "fp32")
+        s.add_species(1.0)
+        s.set_kernel(kernel, 8)
+        s.set_launch(graph_steps=16, use_graph=True, xcd_map=False)
+        s.bind(stream=stream)
+        s.set_field(0, c0)
+        torch.cuda.synchronize()
+        return s
+
+    single = sim(torch.cuda.current_stream(), "block")
+    side = torch.cuda.Stream()
+    s = sim(side, "column")
+    out = torch.zeros(shape, device="cuda")
+    act = torch.as_tensor(img, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        s.get_field(0, out) if call == "get" else s.set_field(0, c1)
+    for _ in range(2):
+        s.step(0.0625, between)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        single.step(0.0625, between)
+        if call == "set":
+            single.set_field(0, c1)
+            s.step(0.0625, between)
+            single.step(0.0625, between)
+            s.get_field(0, out)
+        torch.cuda.synchronize()
+        assert torch.equal(out * act, single.get_field(0) * act)
