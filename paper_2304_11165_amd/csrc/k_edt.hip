@@ -63,7 +63,7 @@ dim3 edt_grid(int64_t n)
 // in a row: the lines it reads are then shared in its own L2.
 __device__ __forceinline__ uint32_t xcd_range()
 {
-    return blockIdx.y * gridDim.x + (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    return blockIdx.y * (uint32_t)EDT_GRID_ROW + (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
 }
 
 // The summary word of a wave's 64 words: the one nearest 0 if all are of one phase, else 0
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void k_edt_x(const uint8_t *__restrict__ img, 
                                                int *__restrict__ g, int *__restrict__ sum)
 {
     extern __shared__ uint64_t words[];  // 4 waves x chunks of 64 voxels
-    const int64_t row = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int64_t row = ((int64_t)blockIdx.y * EDT_GRID_ROW + blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (row >= nrows) return;  // whole waves; no workgroup barrier below
     const int nc = (nx + 63) / 64;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void k_edt_runs(const int *__restrict__ sum, i
                                                   int *__restrict__ c64)
 {
     const int n64 = (n + 63) / 64, n256 = (n + 255) / 256, lane = threadIdx.x & 63;
-    const int64_t wave = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6), l = wave / n256;
+    const int64_t wave = ((int64_t)blockIdx.y * EDT_GRID_ROW + blockIdx.x) * 4 + (threadIdx.x >> 6), l = wave / n256;
     if (l >= nlines) return;
     const int r0 = (int)(wave % n256) * 4;
     int w[4];

@@ -518,10 +518,8 @@ rd_status rd_sim::upload(bool index)
     if (L.cp_stride > 0 && cp_slots > 0)
         LAUNCHCHK(rd_launch_fill_u32(ws + L.cp, 0u, (int64_t)(L.cp_stride * (size_t)cp_slots / 4), stream));
     LAUNCHCHK(rd_launch_fill_u32(ws + L.res, 0u, 64 * 2, stream));  // results + step counter
-    if (!host_res) {
-        HIPCHK(hipHostMalloc((void **)&host_res, 64 * sizeof(double), hipHostMallocDefault));
-        HIPCHK(hipHostGetDevicePointer((void **)&host_res_dev, host_res, 0));
-    }
+    if (!host_res) HIPCHK(hipHostMalloc((void **)&host_res, 64 * sizeof(double), hipHostMallocDefault));
+    if (!host_res_dev) HIPCHK(hipHostGetDevicePointer((void **)&host_res_dev, host_res, 0));
     cur = 0;
     steps_taken = 0;
     for (int s = 0; s < S; ++s) {
