@@ -151,8 +151,8 @@ __device__ __forceinline__ int pix(int x, int y) { return (y + 1) * 10 + (x + 1)
 // The operations per voxel are rd_update_e's, in its order, with a face toward an
 // inactive neighbour weighted 0 (which leaves the sum as it is) and each z face's weight
 // and difference formed once for the two voxels it joins (they differ in sign only).
-// Bound by memory traffic (about 6.5 TB/s past L2 on the half-full blocks of the 320^3 soil
-// volume, two species: 68.0 us); with a test of code bits and a select per species and face,
+// Bound by memory traffic (343 MB past L2 on the half-full blocks of the 320^3 soil volume, two
+// species, in 68.0 us: 5.0 TB/s, the rate of a large copy); with a test of code bits and a select per species and face,
 // 950 vector instructions per wave instead of 695, it took 69.5 us, and on volumes of one
 // round of waves (160^3 packing, one species) 15.7 us instead of 14.5.
 template <typename T, int S, bool XCH, bool BAND>
