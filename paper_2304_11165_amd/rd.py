@@ -429,13 +429,25 @@ class Sim:
         return self
 
     def get_field(self, species, out=None):
+        """Dense (nz, ny, nx) float32 field.  It is written on the simulation's stream; if the
+        caller's current stream is another one, each waits for the other (unless one of them is
+        being captured), so that the tensor can be read there like any other."""
         import torch
 
         nz, ny, nx = self.geometry.shape
         if out is None:
             out = torch.empty((nz, ny, nx), dtype=torch.float32, device=self.workspace.device)
+        cur = torch.cuda.current_stream(self.workspace.device)
+        apart = cur != self.stream and not torch.cuda.is_current_stream_capturing()
+        if apart:
+            with torch.cuda.stream(self.stream):
+                apart = not torch.cuda.is_current_stream_capturing()
+        if apart:
+            self.stream.wait_stream(cur)  # the memory may still be in use there
         _check(_lib.rd_sim_get_field(self.handle, int(species), ctypes.c_void_p(out.data_ptr())),
                "rd_sim_get_field")
+        if apart:
+            cur.wait_stream(self.stream)
         return out
 
     # time stepping --------------------------------------------------------------
